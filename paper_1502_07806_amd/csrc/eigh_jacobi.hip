@@ -30,7 +30,6 @@
 namespace pfsm {
 namespace {
 
-constexpr int NT = 256;
 constexpr int B2 = 2 * EIGH_B;   // 64: order of a pair problem / apply tile
 constexpr int LS = B2 + 1;       // LDS row stride
 constexpr double TOL = 1.1102230246251565e-16;  // 2^-53
@@ -126,49 +125,39 @@ __global__ void sweep_begin(EighBatch e, int sweep) {
 }
 
 // ------------------------------------------------------------------ pair solve
-// Sum over the 8 lanes of an aligned lane group with DPP moves (no LDS
-// round trip): quad_perm [1,0,3,2], quad_perm [2,3,0,1], then the half-row
-// mirror (lane i <-> 7 - i) pairs the two quads.  Every lane of the group
-// ends with the bitwise same sum (IEEE addition is commutative), so lanes
-// that decide on a rotation independently always agree.
-template <int CTRL> __device__ inline double dpp_d(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp((int)b, (int)b, CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp((int)(b >> 32), (int)(b >> 32), CTRL, 0xf, 0xf, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+// Lane exchanges of doubles on the vector unit (no LDS): DPP moves inside a
+// row of 16 lanes, and the half-wave and row swaps.
+__device__ inline int lo_d(double v) { return (int)__double_as_longlong(v); }
+__device__ inline int hi_d(double v) { return (int)(__double_as_longlong(v) >> 32); }
+__device__ inline double mk_d(int lo, int hi) { return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo); }
+constexpr int DPP_FROM_RIGHT = 0x101;  // row_shl:1: lane l takes lane l + 1 of its row, lane 15 keeps `old`
+constexpr int DPP_FROM_LEFT = 0x111;   // row_shr:1: lane l takes lane l - 1 of its row, lane 0 keeps `old`
+template <int CTRL> __device__ inline double dpp_d(double old, double v) {
+  return mk_d(__builtin_amdgcn_update_dpp(lo_d(old), lo_d(v), CTRL, 0xf, 0xf, false),
+              __builtin_amdgcn_update_dpp(hi_d(old), hi_d(v), CTRL, 0xf, 0xf, false));
 }
-__device__ inline double sum8(double v) {
-  v += dpp_d<0xB1>(v);
-  v += dpp_d<0x4E>(v);
-  v += dpp_d<0x141>(v);
-  return v;
+// lanes 32-63 of a change places with lanes 0-31 of b
+__device__ inline void swap32_d(double& a, double& b) {
+  const auto l = __builtin_amdgcn_permlane32_swap(lo_d(a), lo_d(b), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(hi_d(a), hi_d(b), false, false);
+  a = mk_d(l[0], h[0]);
+  b = mk_d(l[1], h[1]);
 }
-// Sum over an aligned group of 16 lanes: the 8-lane sums, then the row mirror
-// (lane i <-> 15 - i) adds the other half (bitwise the same in every lane).
-__device__ inline double sum16(double v) {
-  v = sum8(v);
-  v += dpp_d<0x140>(v);
-  return v;
+// rows 1 and 3 (of 16 lanes) of a change places with rows 0 and 2 of b
+__device__ inline void swap16_d(double& a, double& b) {
+  const auto l = __builtin_amdgcn_permlane16_swap(lo_d(a), lo_d(b), false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(hi_d(a), hi_d(b), false, false);
+  a = mk_d(l[0], h[0]);
+  b = mk_d(l[1], h[1]);
 }
-// The pair solver gives each column pair PL lanes of B2 / PL rows each;
-// a workgroup has PS_NT = 32 PL threads.
-constexpr int PL = 16;
-constexpr int PS_NT = 32 * PL;
-__device__ inline double sum_pl(double v) { return PL == 16 ? sum16(v) : sum8(v); }
-// Reciprocal and reciprocal square root: the hardware estimates (relative
-// error about 5e-8) refined by two Newton steps, which converge
-// quadratically to one or two ulps (measured: 1.9e-16 and 2.3e-16).
-__device__ inline double rcp_d(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) r = r * (2.0 - x * r);
-  return r;
-}
+// Reciprocal square root: the hardware estimate r (relative error about 5e-8)
+// and one third-order step r (1 + e / 2 + 3 e^2 / 8), e = 1 - x r^2, whose
+// error e^3 / 3 vanishes below the rounding: four dependent operations, half
+// of what two Newton steps need.
 __device__ inline double rsq_d(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) r = r * (1.5 - 0.5 * x * r * r);
-  return r;
+  const double r = __builtin_amdgcn_rsq(x);
+  const double e = fma(-(x * r), r, 1.0);
+  return fma(r * e, fma(0.375, e, 0.5), r);
 }
 
 // The 2b x 2b pair problem S = [B_II B_IJ; B_JI B_JJ] is diagonalised by a
@@ -176,147 +165,205 @@ __device__ inline double rsq_d(double x) {
 // bound| so that W is positive definite: column pairs of W are rotated until
 // all columns are orthogonal.  Then W = W0 R = R diag(lambda + sigma) for
 // the accumulated rotation R, so the eigenvectors are the normalised final
-// columns of W and R is never accumulated.  PL = 16 lanes own a column pair
-// (4 rows each, two waves per SIMD) and reduce its inner product with DPP, so
-// a round needs one barrier; the squared column norms are summed exactly in the first round of
-// each sweep and carried through the rotations in the others.  Padding
-// indices (beyond the submatrix order) never rotate.
+// columns of W and R is never accumulated.  Padding columns (beyond the
+// submatrix order) are unit vectors whose products with every other column
+// are exactly zero, so they never rotate.
+//
+// W stays in registers.  The tournament's positions form 32 slots (s, 63 - s);
+// lane j of each row of 16 lanes holds slots 2j and 2j + 1 (columns T0, B0,
+// T1, B1), and the PS_W waves' 4 PS_W rows of lanes hold PS_R rows of W each.
+// Between rounds the columns move one position along the ring: T1 <- T0 of
+// the right neighbour, B0 <- B1 of the left one (DPP moves, whose kept `old`
+// values are the ring's two turns), B1 <- B0 and T0 <- T1 inside the lane
+// (T0 of slot 0 stays); 63 rounds bring every column back.  A round sums the
+// inner products of a lane's two pairs over its rows, then over the wave's
+// four rows of lanes with the half and row swaps, which leave slot 2j's sum
+// in lanes 0-31 and slot 2j + 1's in lanes 32-63, then over the waves through
+// LDS (one barrier per round, two buffers).  Each lane works out one rotation
+// and shares it with the other half.  The squared column norms are summed
+// exactly in the first round of each sweep and travel with their columns,
+// updated by each rotation, in the others.  All waves hold the same sums, so
+// they agree on every rotation and on the stopping test without further
+// exchange.
+//
+// A round is a latency chain (inner product, exchange, two reciprocal square
+// roots, rotation) and the issue of about 200 instructions per wave: 0.52 us
+// with one workgroup per CU, 1.5 us for four (a submatrix sweep of the N = 8192
+// mixed step 2.9 -> 2.4 ms; full diagonalisation at N = 1024 60.2 -> 48.3 ms).  W in LDS with 16 lanes per
+// column pair and eight waves took 0.9 us (64 KB of LDS traffic per round and
+// the scalar chain issued for four pairs at a time); one column per lane with
+// ds_bpermute took 0.82 us (a permute costs about 8 cycles of the CU's LDS).
+constexpr int PS_W = 4;               // waves of a pair problem
+constexpr int PS_NT = 64 * PS_W;      // threads
+constexpr int PS_R = B2 / (4 * PS_W); // rows of W per lane
 struct SolveLds {
-  double W[B2][LS];  // column-major: W[col][row]
-  double nrm[B2];
-  double cn[B2];     // running squared column norms of W
-  int any_rot;
-  int sweep_rot;
+  double part[2][PS_W][32];  // partial inner products per slot, by round parity
+  double nrm[4 * PS_W][B2];  // partial squared norms per column
 };
 // Pair problem k of submatrix p in the given round (PS_NT threads).
 __device__ void solve_pair(const EighBatch& e, int round, int p, int k, SolveLds& L) {
   const int npairs = e.nb / 2;
   int* flagR = flag_buf(e, round) + (int64_t)p * npairs + k;
   if (e.state[2 * p]) { if (threadIdx.x == 0) *flagR = 0; return; }
-  double (*W)[LS] = L.W;
-  double* nrm = L.nrm;
-  double* cn = L.cn;
-  int& any_rot = L.any_rot;
-  int& sweep_rot = L.sweep_rot;
   const int Mp = e.Mp;
   const int msize = e.wsize[p];
   int I, J;
   pair_blocks(k, round, e.nb, I, J);
   const double* B = e.Bw + (int64_t)p * Mp * Mp;
-  const int tid = threadIdx.x;
+  const int lane = threadIdx.x & 63, j = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int group = 4 * wave + (lane >> 4), row0 = PS_R * group;
+  const bool upper = lane >= 32;             // works on slot 2j + 1
+  const int slot = 2 * j + (upper ? 1 : 0);
   const double fl = noise_floor(e, p);
-  // pass 1: copy S (as columns) and decide whether any rotation is needed
-  if (tid == 0) any_rot = 0;
-  __syncthreads();
+  // the lane's rows of columns 2j, 2j + 1 (T0, T1) and 62 - 2j, 63 - 2j (B1,
+  // B0), read along the rows of the symmetric B, and whether any entry needs
+  // a rotation
+  const int ct = pair_idx(2 * j, I, J), cb = pair_idx(62 - 2 * j, I, J);
+  double T0[PS_R], T1[PS_R], B0[PS_R], B1[PS_R], dr[PS_R];
+#pragma unroll
+  for (int m = 0; m < PS_R; ++m) {
+    const int gr = pair_idx(row0 + m, I, J);
+    const double* row = B + (int64_t)gr * Mp;
+    const double2 t = *(const double2*)(row + ct), b = *(const double2*)(row + cb);
+    T0[m] = t.x; T1[m] = t.y; B1[m] = b.x; B0[m] = b.y;
+    dr[m] = row[gr];
+  }
+  double dc[4];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    dc[u] = B[(ct + u) * (int64_t)(Mp + 1)];
+    dc[2 + u] = B[(cb + u) * (int64_t)(Mp + 1)];
+  }
   int need = 0;
-  {  // every load in flight before the first store (a loop would wait for each in turn)
-    constexpr int PER = B2 * B2 / PS_NT;
-    double v[PER];
+  auto test = [&](double v, int row, int col, double a, double b) {
+    if (row < col && fabs(v) > fl && must_rotate(v, a, b, fl)) need = 1;
+  };
 #pragma unroll
-    for (int m = 0; m < PER; ++m) {
-      const int idx = tid + PS_NT * m, r = idx % B2, c = idx / B2;
-      v[m] = B[pair_idx(r, I, J) + (int64_t)pair_idx(c, I, J) * Mp];
-    }
-#pragma unroll
-    for (int m = 0; m < PER; ++m) {
-      const int idx = tid + PS_NT * m, r = idx % B2, c = idx / B2;
-      W[c][r] = v[m];
-    }
+  for (int m = 0; m < PS_R; ++m) {
+    test(T0[m], row0 + m, 2 * j, dr[m], dc[0]);
+    test(T1[m], row0 + m, 2 * j + 1, dr[m], dc[1]);
+    test(B1[m], row0 + m, 62 - 2 * j, dr[m], dc[2]);
+    test(B0[m], row0 + m, 63 - 2 * j, dr[m], dc[3]);
   }
-  __syncthreads();
-  for (int idx = tid; idx < B2 * B2; idx += PS_NT) {
-    int r = idx % B2, c = idx / B2;
-    if (r < c && must_rotate(W[c][r], W[r][r], W[c][c], fl)) need = 1;
-  }
-  if (need) any_rot = 1;
-  __syncthreads();
-  if (!any_rot) { if (tid == 0) *flagR = 0; return; }
+  if (!__syncthreads_or(need)) { if (threadIdx.x == 0) *flagR = 0; return; }
   const double* sc = scal_of(e, p);
   const double sigma = 2.0 * fmax(fabs(sc[1]), fabs(sc[2])) + TINY;
-  for (int t = tid; t < B2; t += PS_NT) {
-    const bool pad = pair_idx(t, I, J) >= msize;
-    if (pad) {  // a padding column becomes a unit vector (no overflow, never rotated)
-      for (int r = 0; r < B2; ++r) W[t][r] = (r == t) ? 1.0 : 0.0;
-    } else {
-      W[t][t] += sigma;
-    }
+  auto shift = [&](double v, int row, int col, int gcol) {
+    const bool diag = row == col;
+    return gcol >= msize ? (diag ? 1.0 : 0.0) : (diag ? v + sigma : v);
+  };
+#pragma unroll
+  for (int m = 0; m < PS_R; ++m) {
+    T0[m] = shift(T0[m], row0 + m, 2 * j, ct);
+    T1[m] = shift(T1[m], row0 + m, 2 * j + 1, ct + 1);
+    B1[m] = shift(B1[m], row0 + m, 62 - 2 * j, cb);
+    B0[m] = shift(B0[m], row0 + m, 63 - 2 * j, cb + 1);
   }
-  __syncthreads();
-  const int slot = tid / PL, sub = tid % PL;  // 32 column pairs x PL lanes
+  // exact squared norms of the lane's four columns (all start positions: the
+  // columns are back in place at the start of every sweep)
+  double nT0, nT1, nB0, nB1;
+  auto exact_norms = [&]() {
+    double a = 0.0, b = 0.0, c = 0.0, d = 0.0;
+#pragma unroll
+    for (int m = 0; m < PS_R; ++m) {
+      a = fma(T0[m], T0[m], a);
+      b = fma(T1[m], T1[m], b);
+      c = fma(B1[m], B1[m], c);
+      d = fma(B0[m], B0[m], d);
+    }
+    *(double2*)&L.nrm[group][2 * j] = make_double2(a, b);
+    *(double2*)&L.nrm[group][62 - 2 * j] = make_double2(c, d);
+    __syncthreads();
+    nT0 = nT1 = nB0 = nB1 = 0.0;
+#pragma unroll
+    for (int g = 0; g < 4 * PS_W; ++g) {
+      const double2 t = *(const double2*)&L.nrm[g][2 * j], u = *(const double2*)&L.nrm[g][62 - 2 * j];
+      nT0 += t.x;
+      nT1 += t.y;
+      nB1 += u.x;
+      nB0 += u.y;
+    }
+  };
+  const bool first = j == 0;
+  auto move = [&](double& t0, double& b0, double& t1, double& b1) {
+    const double nt1 = dpp_d<DPP_FROM_RIGHT>(b1, t0), nb0 = dpp_d<DPP_FROM_LEFT>(t1, b1);
+    t0 = first ? t0 : t1;
+    b1 = b0;
+    t1 = nt1;
+    b0 = nb0;
+  };
   const double angle = e.angle > 0.0 ? e.angle : ANGLE;
   bool converged = false;
+  int par = 0;
   for (int sweep = 0; sweep < e.inner_max_sweeps; ++sweep) {
-    if (tid == 0) sweep_rot = 0;
-    __syncthreads();
+    unsigned long long big = 0;  // lanes that rotated by more than the stopping angle
+    exact_norms();
+#pragma unroll 1
     for (int r = 0; r < B2 - 1; ++r) {
-      const int a = rr_index(slot, r, B2), b = rr_index(B2 - 1 - slot, r, B2);
-      const int pc = min(a, b), qc = max(a, b);
-      double x[B2 / PL], y[B2 / PL];
-      double ab = 0.0, aa, bb;
-      if (r == 0) {
-        // exact squared column norms at the start of each sweep (every
-        // column is in exactly one pair of a round); later rounds use the
-        // running values in cn, updated with each rotation
-        double sa = 0.0, sb = 0.0;
+      double p0 = 0.0, p1 = 0.0;
 #pragma unroll
-        for (int m = 0; m < B2 / PL; ++m) {
-          const int row = sub + PL * m;
-          x[m] = W[pc][row];
-          y[m] = W[qc][row];
-          sa += x[m] * x[m];
-          sb += y[m] * y[m];
-          ab += x[m] * y[m];
-        }
-        aa = sum_pl(sa);
-        bb = sum_pl(sb);
-      } else {
-#pragma unroll
-        for (int m = 0; m < B2 / PL; ++m) {
-          const int row = sub + PL * m;
-          x[m] = W[pc][row];
-          y[m] = W[qc][row];
-          ab += x[m] * y[m];
-        }
-        aa = cn[pc];
-        bb = cn[qc];
+      for (int m = 0; m < PS_R; ++m) {
+        p0 = fma(T0[m], B0[m], p0);
+        p1 = fma(T1[m], B1[m], p1);
       }
-      ab = sum_pl(ab);
-      const bool padpair = pair_idx(pc, I, J) >= msize || pair_idx(qc, I, J) >= msize;
-      double na = aa, nb = bb;
+      swap32_d(p0, p1);
+      double ab = p0 + p1, other = ab;
+      swap16_d(ab, other);
+      ab += other;
+      if (!(lane & 16)) L.part[par][wave][slot] = ab;
+      __syncthreads();
+      ab = L.part[par][0][slot];
+#pragma unroll
+      for (int w = 1; w < PS_W; ++w) ab += L.part[par][w][slot];
+      par ^= 1;
+      const double aa = upper ? nT1 : nT0, bb = upper ? nB1 : nB0;
       // columns count as orthogonal below 8 u relative (|ab| <= 8u sqrt(aa bb),
       // compared squared): the rounding noise of the dot products stays under
       // it, so converged pairs stop rotating
-      if (!padpair && fabs(ab) > TINY && ab * ab > (64.0 * TOL * TOL) * (aa * bb)) {
-        // tan 2t = 2 ab / (bb - aa), |t| <= pi/4, from r = sqrt(d^2 + 4 ab^2):
-        // cos 2t = |d| / r, cos^2 t = (1 + cos 2t) / 2, sin t = sin 2t / (2 cos t)
-        const double d = bb - aa;
-        const double ir = rsq_d(fma(d, d, 4.0 * ab * ab));
-        const double h = fma(0.5 * fabs(d), ir, 0.5);
-        const double ic = rsq_d(h);
-        const double c = h * ic;
-        const double sn = (d >= 0.0 ? ab : -ab) * ir * ic;
+      const bool rot = fabs(ab) > TINY && ab * ab > (64.0 * TOL * TOL) * (aa * bb);
+      // tan 2t = 2 ab / (bb - aa), |t| <= pi/4, from r = sqrt(d^2 + 4 ab^2):
+      // cos 2t = |d| / r, cos^2 t = (1 + cos 2t) / 2, sin t = sin 2t / (2 cos t)
+      const double d = bb - aa;
+      const double ir = rsq_d(fma(d, d, 4.0 * ab * ab));
+      const double h = fma(0.5 * fabs(d), ir, 0.5);
+      const double ic = rsq_d(h);
+      bool pos = d > 0.0;
+      if (__ballot(d == 0.0)) {  // equal norms: the column of lower index takes the minus sign
+        const int it = slot == 0 ? 0 : (slot - 1 + r) % (B2 - 1) + 1, ib = (62 - slot + r) % (B2 - 1) + 1;
+        if (d == 0.0) pos = it < ib;
+      }
+      double s0 = (pos ? ab : -ab) * ir * ic, c0 = h * ic;
+      c0 = rot ? c0 : 1.0;
+      s0 = rot ? s0 : 0.0;
+      // only rotations by more than the stopping angle keep the sweep going (see above)
+      big |= __ballot(fabs(s0) > angle);
+      double x0 = 2.0 * c0 * s0 * ab, c1 = c0, s1 = s0, x1 = x0;
+      swap32_d(c0, c1);
+      swap32_d(s0, s1);
+      swap32_d(x0, x1);
+      {
+        const double cc = c0 * c0, ss = s0 * s0, a = nT0, b = nB0;
+        nT0 = fma(cc, a, fma(ss, b, -x0));
+        nB0 = fma(ss, a, fma(cc, b, x0));
+      }
+      {
+        const double cc = c1 * c1, ss = s1 * s1, a = nT1, b = nB1;
+        nT1 = fma(cc, a, fma(ss, b, -x1));
+        nB1 = fma(ss, a, fma(cc, b, x1));
+      }
+      move(nT0, nB0, nT1, nB1);
 #pragma unroll
-        for (int m = 0; m < B2 / PL; ++m) {
-          const int row = sub + PL * m;
-          W[pc][row] = c * x[m] - sn * y[m];
-          W[qc][row] = sn * x[m] + c * y[m];
-        }
-        const double cs2 = 2.0 * c * sn * ab;
-        na = c * c * aa - cs2 + sn * sn * bb;
-        nb = sn * sn * aa + cs2 + c * c * bb;
-        // only rotations by more than the stopping angle keep the sweep going (see above)
-        if (sub == 0 && fabs(sn) > angle) sweep_rot = 1;
+      for (int m = 0; m < PS_R; ++m) {
+        const double t0 = T0[m], b0 = B0[m], t1 = T1[m], b1 = B1[m];
+        T0[m] = fma(-s0, b0, c0 * t0);
+        B0[m] = fma(s0, t0, c0 * b0);
+        T1[m] = fma(-s1, b1, c1 * t1);
+        B1[m] = fma(s1, t1, c1 * b1);
+        move(T0[m], B0[m], T1[m], B1[m]);
       }
-      if (sub == 0) {
-        cn[pc] = na;
-        cn[qc] = nb;
-      }
-      __syncthreads();
     }
-    // every thread reads the flag before thread 0 may clear it for the next sweep
-    const bool again = sweep_rot != 0;
-    __syncthreads();
-    if (!again) {
+    if (!big) {
       converged = true;
       break;
     }
@@ -325,20 +372,17 @@ __device__ void solve_pair(const EighBatch& e, int round, int p, int k, SolveLds
   // column pair is orthogonal; a pair problem that did not get there is a
   // convergence failure of the eigensolver.
   int* inf = info_of(e, p);
-  if (!converged && tid == 0 && inf) atomicCAS(inf, 0, PFSM_INFO_EIGH_NOCONV);
-  // eigenvectors: normalised columns of W
-  if (tid < B2) {
-    double s2 = 0.0;
-    for (int r = 0; r < B2; ++r) s2 += W[tid][r] * W[tid][r];
-    nrm[tid] = rsq_d(s2);
-  }
-  __syncthreads();
+  if (!converged && threadIdx.x == 0 && inf) atomicCAS(inf, 0, PFSM_INFO_EIGH_NOCONV);
+  // eigenvectors: normalised columns of W, row-major: Rg[r * 2b + c] = R(r, c)
+  exact_norms();
+  const double iT0 = rsq_d(nT0), iT1 = rsq_d(nT1), iB0 = rsq_d(nB0), iB1 = rsq_d(nB1);
   double* Rg = rot_buf(e, round) + ((int64_t)p * npairs + k) * B2 * B2;
-  for (int idx = tid; idx < B2 * B2; idx += PS_NT) {  // row-major: Rg[r * 2b + c] = R(r, c)
-    int r = idx / B2, c = idx % B2;
-    Rg[idx] = W[c][r] * nrm[c];
+#pragma unroll
+  for (int m = 0; m < PS_R; ++m) {
+    *(double2*)&Rg[(row0 + m) * B2 + 2 * j] = make_double2(T0[m] * iT0, T1[m] * iT1);
+    *(double2*)&Rg[(row0 + m) * B2 + 62 - 2 * j] = make_double2(B1[m] * iB1, B0[m] * iB0);
   }
-  if (tid == 0) {
+  if (threadIdx.x == 0) {
     *flagR = 1;
     atomicOr(&e.state[2 * p + 1], 1);
     atomicAdd(&e.stats[2 * p + 1], 1);
@@ -537,24 +581,28 @@ template <int NTH> __device__ void apply_u_tile(const EighBatch& e, int round, i
 }
 
 // B tiles of a round: one eight-wave workgroup per tile (four fit a CU).
-__global__ __launch_bounds__(PS_NT) void pair_apply_b(EighBatch e, int round) {
+constexpr int AB_NT = 512;
+__global__ __launch_bounds__(AB_NT) void pair_apply_b(EighBatch e, int round) {
   __shared__ double T[B2][LS];
   const int npairs = e.nb / 2, ntri = npairs * (npairs + 1) / 2;
-  apply_b_tile<PS_NT>(e, round, blockIdx.x / ntri, blockIdx.x % ntri, T);
+  apply_b_tile<AB_NT>(e, round, blockIdx.x / ntri, blockIdx.x % ntri, T);
 }
 
 // The pair problems of round solve_round (the first P * npairs workgroups;
 // none when solve_round < 0) beside the U tiles of round u_round (the rest).
 __global__ __launch_bounds__(PS_NT) void pair_solve_apply_u(EighBatch e, int solve_round, int u_round) {
-  __shared__ SolveLds L;
+  __shared__ union {
+    SolveLds solve;
+    double T[B2][LS];
+  } L;
   const int npairs = e.nb / 2;
   const int ns = solve_round >= 0 ? e.P * npairs : 0;
   const int b = blockIdx.x;
   if (b < ns) {
-    solve_pair(e, solve_round, b / npairs, b % npairs, L);
+    solve_pair(e, solve_round, b / npairs, b % npairs, L.solve);
   } else {
     const int per = (e.Mp / B2) * npairs;
-    apply_u_tile<PS_NT>(e, u_round, (b - ns) / per, (b - ns) % per, L.W);
+    apply_u_tile<PS_NT>(e, u_round, (b - ns) / per, (b - ns) % per, L.T);
   }
 }
 
@@ -624,7 +672,7 @@ static hipError_t eigh_run(const EighBatch& e, const T* At, int64_t ldat, int ma
     const int rounds = e.nb - 1;
     hipLaunchKernelGGL(pair_solve, dim3(e.P * npairs), dim3(PS_NT), 0, s, e, 0);
     for (int r = 0; r < rounds; ++r) {
-      hipLaunchKernelGGL(pair_apply_b, dim3(e.P * (npairs * (npairs + 1) / 2)), dim3(PS_NT), 0, s, e, r);
+      hipLaunchKernelGGL(pair_apply_b, dim3(e.P * (npairs * (npairs + 1) / 2)), dim3(AB_NT), 0, s, e, r);
       const int next = r + 1 < rounds ? r + 1 : -1;
       const unsigned grid = (unsigned)((next >= 0 ? e.P * npairs : 0) + e.P * nrc * npairs);
       hipLaunchKernelGGL(pair_solve_apply_u, dim3(grid), dim3(PS_NT), 0, s, e, next, r);

@@ -56,6 +56,24 @@ def test_full_diag_parity(pf, n, basis):
     assert np.all(np.abs(Vo - V_ref).max(axis=0) <= 100 * tol + 1e-12)
 
 
+@pytest.mark.parametrize("n", [1, 2, 31, 33, 64, 65, 127, 129, 200])
+def test_full_diag_equal_diagonal(pf, n):
+    """Pair problems at the edges of their blocks (padding columns, partly
+    filled last blocks) on the second-difference matrix: its equal diagonal
+    entries give every first-round pair equal column norms (the tie rule of
+    the rotation's sign), and its eigenvalues are 2 - 2 cos(k pi / (n + 1)).
+    A few hundred rotations of norm-4 rows leave about n u 4 = 1e-13 in an
+    eigenvalue and n u in an inner product; 1e-12 covers both at n = 200."""
+    dev = torch.device("cuda:0")
+    A = 2.0 * np.eye(n) - np.eye(n, k=1) - np.eye(n, k=-1)
+    lam, V = pf.FullDiag(n).solve(torch.from_numpy(A).to(dev))
+    lam, V = lam.cpu().numpy(), V.cpu().numpy()
+    want = 2.0 - 2.0 * np.cos(np.arange(1, n + 1) * np.pi / (n + 1))
+    assert np.max(np.abs(lam - want)) <= 1e-12
+    assert np.max(np.abs(V.T @ V - np.eye(n))) <= 1e-12
+    assert np.max(np.abs(A @ V - V * lam)) <= 1e-12
+
+
 def test_scf_sequence_switches_to_pfsm(pf):
     dev = torch.device("cuda:0")
     n = 1024
