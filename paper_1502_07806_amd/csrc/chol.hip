@@ -310,7 +310,7 @@ hipError_t gemm_store(int64_t M, int64_t N, int64_t K, const double* A, int64_t 
   if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
   GemmArgs g = {};
   g.M = M; g.N = N; g.K = K; g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc;
-  g.alpha = alpha; g.beta = beta; g.lower_only = lower;
+  g.alpha = alpha; g.beta = beta; g.lower_only = lower; g.in_place = C == A;
   return gemm_f64(false, tb, EPI_STORE, g, s);
 }
 

@@ -39,15 +39,20 @@ struct GemmArgs {
   const double* alpha_dev;   // optional device scalar for EPI_FSUPD
   const double* eps;         // column shifts for EPI_SHIFT / EPI_FSUPD, row scales for EPI_G2S
   const double* D; int64_t ldd;  // FSUPD base matrix / RQ partner matrix
-  double* part;              // RQ partial sums [tiles_m x N]
-  double* part2;             // RQ, optional: partial sums of acc^2 [tiles_m x N] (squared column norms of A X)
+  double* part;              // RQ / G2S partial sums [ceil(M / part_rows) x N]
+  double* part2;             // RQ, optional: partial sums of acc^2 (as part; squared column norms of A X)
+  int part_rows;             // rows per partial sum: 128 (or 0), 64 or 32, from gemm_f64_tile
   const int32_t* krange;     // optional [tiles_n][2] K range per column tile
-  int lower_only;            // skip tiles strictly above the diagonal
+  int lower_only;            // skip tiles strictly above the diagonal; RQ: A is symmetric, only its blocks on
+                             // and below the diagonal are read (not with part2)
+  int in_place;              // C aliases A: N must fit one column tile (N <= 64)
 };
 
 constexpr int GEMM_BM = 128, GEMM_BN = 128, GEMM_BK = 16;
 
 hipError_t gemm_f64(bool ta, bool tb, int epi, const GemmArgs& a, hipStream_t s);
+// Block tile (128, 64 or 32) of an M x N product; lower: lower tiles only.
+int gemm_f64_tile(int64_t M, int64_t N, bool lower);
 
 // ---------------------------------------------------------------- misc kernels
 hipError_t mirror_lower(double* C, int64_t n, int64_t ldc, hipStream_t s);

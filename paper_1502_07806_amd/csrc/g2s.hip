@@ -78,14 +78,14 @@ __global__ __launch_bounds__(NT) void k_g2s_res(const double* blk, const double*
 }  // namespace
 
 size_t g2s_workspace_bytes(int64_t n) {
-  const int64_t tiles_m = (n + GEMM_BM - 1) / GEMM_BM;
+  const int64_t rows = gemm_f64_tile(n, n, false), tiles_m = (n + rows - 1) / rows;
   return al256((size_t)n * n * sizeof(double)) + al256((size_t)n * sizeof(double)) +
          al256((size_t)tiles_m * n * sizeof(double)) + al256((size_t)n * sizeof(double)) +
          al256((size_t)RB * sizeof(double));
 }
 
 G2SWork g2s_carve(void* base, int64_t n) {
-  const int64_t tiles_m = (n + GEMM_BM - 1) / GEMM_BM;
+  const int64_t rows = gemm_f64_tile(n, n, false), tiles_m = (n + rows - 1) / rows;
   char* p = (char*)base;
   G2SWork w;
   w.zbuf = (double*)p;
@@ -102,7 +102,7 @@ G2SWork g2s_carve(void* base, int64_t n) {
 
 hipError_t g2s_run(int64_t n, const double* A, int64_t lda, const double* B, int64_t ldb, int iterations, double* Z,
                    int64_t ldz, G2SWork w, double* res, int* info, hipStream_t s) {
-  const int64_t tiles_m = (n + GEMM_BM - 1) / GEMM_BM;
+  const int64_t rows = gemm_f64_tile(n, n, false), tiles_m = (n + rows - 1) / rows;
   hipError_t e = fill_i32(info, 1, 0, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_g2s_dinv, dim3((unsigned)((n + NT - 1) / NT)), dim3(NT), 0, s, B, ldb, n, w.dinv, info);
@@ -118,7 +118,7 @@ hipError_t g2s_run(int64_t n, const double* A, int64_t lda, const double* B, int
   for (int k = 0; k < iterations; ++k) {
     GemmArgs g = {};
     g.M = n; g.N = n; g.K = n; g.A = B; g.lda = ldb; g.B = cur; g.ldb = ldc; g.C = nxt; g.ldc = ldn;
-    g.D = A; g.ldd = lda; g.eps = w.dinv; g.part = w.part;
+    g.D = A; g.ldd = lda; g.eps = w.dinv; g.part = w.part; g.part_rows = (int)rows;
     e = gemm_f64(true, false, EPI_G2S, g, s);  // B symmetric: B^T Z = B Z in the faster TN layout
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_g2s_res_part, dim3(RB), dim3(NT), 0, s, w.part, tiles_m * n, w.blk);

@@ -490,7 +490,17 @@ static pfsm_status solve_fp64(pfsm_plan* pl, const double* dA, int64_t lda, cons
   double* lamu = (double*)(W + pl->o_lamu);
   double* part = (double*)(W + pl->o_part);
   double* scal = (double*)(W + pl->o_scal);
-  const int tiles_m = (int)((n + GEMM_BM - 1) / GEMM_BM);
+  // Partial sums of the Rayleigh quotients, one row per block tile of their
+  // product: in their own array (tiles of 128), or for smaller tiles in the
+  // submatrices' array, which is free once the start vectors are embedded.
+  int part_rows = gemm_f64_tile(n, n, false);
+  if (part_rows < GEMM_BM) {
+    const int64_t rows = (n + part_rows - 1) / part_rows * (pl->residuals ? 2 : 1);
+    if (rows * n <= (int64_t)pl->P * pl->Mp * pl->Mp) part = (double*)(W + pl->o_Bw);
+    else part_rows = GEMM_BM;
+  }
+  const int tiles_m = (int)((n + part_rows - 1) / part_rows);
+  double* part2 = part_rows < GEMM_BM ? part + (int64_t)tiles_m * n : (double*)(W + pl->o_part2);
 
   StageClock clk(pl, s);
   if (phase != PH_END) {
@@ -532,8 +542,8 @@ static pfsm_status solve_fp64(pfsm_plan* pl, const double* dA, int64_t lda, cons
     if (pl->shift_mode == PFSM_SHIFT_RAYLEIGH) {
       GemmArgs r = {};
       r.M = n; r.N = n; r.K = n; r.A = At; r.lda = n; r.B = X; r.ldb = n; r.D = X; r.ldd = n; r.part = part;
-      r.alpha = 1.0;
-      PFSM_TRY(gemm_f64(true, false, EPI_RQ, r, s));  // At symmetric
+      r.alpha = 1.0; r.part_rows = part_rows; r.lower_only = 1;  // At symmetric
+      PFSM_TRY(gemm_f64(true, false, EPI_RQ, r, s));
       PFSM_TRY(col_norm2(X, n, n, n, (double*)(W + pl->o_den), s));
       PFSM_TRY(rq_reduce(part, tiles_m, n, (double*)(W + pl->o_den), eps, s));
     }
@@ -577,8 +587,11 @@ static pfsm_status solve_fp64(pfsm_plan* pl, const double* dA, int64_t lda, cons
   {
     GemmArgs r = {};
     r.M = n; r.N = n; r.K = n; r.A = At; r.lda = n; r.B = X; r.ldb = n; r.D = X; r.ldd = n; r.part = part;
-    r.alpha = 1.0;
-    if (pl->residuals) r.part2 = (double*)(W + pl->o_part2);
+    r.alpha = 1.0; r.part_rows = part_rows;
+    // without the residuals, x^T At x from the blocks of At on and below the
+    // diagonal alone (half of the product; At is symmetric)
+    if (pl->residuals) r.part2 = part2;
+    else r.lower_only = 1;
     PFSM_TRY(gemm_f64(true, false, EPI_RQ, r, s));
     PFSM_TRY(rq_reduce(part, tiles_m, n, nullptr, lamu, s));
     if (pl->residuals) PFSM_TRY(rq_reduce(r.part2, tiles_m, n, nullptr, (double*)(W + pl->o_zz), s));

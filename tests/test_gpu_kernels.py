@@ -56,6 +56,68 @@ def test_gemm_f64_store(dev, ta, tb, M, N, K):
     assert np.max(np.abs(_np(dC) - ref)) <= bound
 
 
+@pytest.mark.parametrize("ta,tb", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("M,N,K,pad", [
+    (2048, 2048, 40, 0), (2047, 2047, 41, 0), (2046, 2048, 7, 1), (2048, 2046, 2, 0),  # tiles of 128: 16- and 4-byte loads
+    (1300, 1282, 334, 0), (1301, 1283, 333, 0), (1300, 1282, 16, 1),                   # tiles of 64
+    (65, 1, 31, 0), (640, 640, 33, 0), (1, 1, 1, 0)])                                   # tiles of 32
+def test_gemm_f64_tiles(dev, ta, tb, M, N, K, pad):
+    """Every tile size and load width at ragged edges and K remainders; pad:
+    odd leading dimensions under even sizes.  Bound as above."""
+    g = np.random.default_rng(M * 7 + N + K)
+    A = g.standard_normal((K, M) if ta else (M, K))
+    B = g.standard_normal((N, K) if tb else (K, N))
+
+    def cm(x):
+        t = torch.full((x.shape[1], x.shape[0] + pad), float("nan"), dtype=torch.float64, device=dev)
+        t[:, :x.shape[0]] = torch.from_numpy(np.ascontiguousarray(x.T)).to(dev)
+        return t
+
+    dA, dB = cm(A), cm(B)
+    dC = torch.zeros((N, M), dtype=torch.float64, device=dev)
+    rc = lib().pfsm_test_gemm_f64(ta, tb, 0, M, N, K, _p(dA), dA.shape[1], _p(dB), dB.shape[1], _p(dC), M, 1.0, 0.0,
+                                  None, None, 0, None, 0, _stream())
+    assert rc == 0
+    ref = (A.T if ta else A) @ (B.T if tb else B)
+    bound = 2 * K * U64 * np.abs(A).max() * np.abs(B).max() * K
+    assert np.max(np.abs(dC.cpu().numpy().T - ref)) <= bound
+
+
+def test_gemm_f64_long_columns(dev):
+    """Leading dimensions past the 31-bit tile offsets (2^21 doubles)."""
+    ld = (1 << 21) + 1
+    g = np.random.default_rng(3)
+    A, B = g.standard_normal((5, 3)), g.standard_normal((3, 4))
+    dA = torch.zeros(3 * ld, dtype=torch.float64, device=dev).view(3, ld)
+    dA[:, :5] = torch.from_numpy(np.ascontiguousarray(A.T)).to(dev)
+    dB = _cm(B, dev)
+    dC = torch.zeros((4, 5), dtype=torch.float64, device=dev)
+    assert lib().pfsm_test_gemm_f64(0, 0, 0, 5, 4, 3, _p(dA), ld, _p(dB), 3, _p(dC), 5, 1.0, 0.0, None, None, 0, None,
+                                    0, _stream()) == 0
+    assert np.max(np.abs(dC.cpu().numpy().T - A @ B)) <= 18 * U64 * np.abs(A).max() * np.abs(B).max()
+
+
+@pytest.mark.parametrize("n", [127, 300, 515])
+def test_gemm_f64_rq_symmetric(dev, n):
+    """Rayleigh quotients from the blocks of a symmetric matrix on and below
+    the diagonal: the blocks above it hold NaN and must not be read."""
+    g = np.random.default_rng(n)
+    A = g.standard_normal((n, n))
+    A = 0.5 * (A + A.T)
+    X = g.standard_normal((n, n))
+    Al = A.copy()
+    for i in range(0, n, 128):
+        Al[i:i + 128, i + 128:] = np.nan  # A(row, k) of a row tile: k past its diagonal block
+    dA, dX = _cm(Al.T.copy(), dev), _cm(X, dev)  # op(A) = A^T
+    tiles_m = (n + 127) // 128
+    part = torch.empty(tiles_m * n, dtype=torch.float64, device=dev)
+    assert lib().pfsm_test_gemm_f64(1, 0, 3, n, n, n, _p(dA), n, _p(dX), n, None, n, 1.0, 0.0, None, _p(dX), n,
+                                    _p(part), 1, _stream()) == 0
+    rq = _np(part).reshape(tiles_m, n).sum(0)
+    tol = 40 * n * U64 * np.abs(A).max() * np.abs(X).max() * n
+    assert np.max(np.abs(rq - np.sum(X * (A @ X), 0))) <= tol
+
+
 def test_gemm_f64_epilogues(dev):
     n = 300
     g = np.random.default_rng(5)
