@@ -32,7 +32,7 @@ struct EighBatch {
   double* Uw;              // [P][Mp][Mp] accumulated eigenvectors
   double* Rw;              // [2][P][nb/2][2b][2b] pair rotations, by round parity
   int* rflag;              // [2][P][nb/2] 1 if the pair's rotation is not the identity, by round parity
-  int* state;              // [P][2] {done, rotated-this-sweep}
+  int* state;              // [P][2] {last sweep that rotated, last sweep that ran} (1-based)
   int* stats;              // [P][2] {sweep found converged (0: not), rotating pair problems}
   int* sel;                // [P][Mp] ascending rank -> local index
   const int64_t* wstart;   // [P] first row/column of the submatrix in At

@@ -15,9 +15,9 @@
 //             pair problems (nothing reads U in between).
 //
 // (The pair problem is solved by a one-sided Jacobi, see solve_pair.)
-// A sweep in which no pair needed a rotation marks the submatrix converged;
-// later kernels of that submatrix return immediately.  A pair (p, q) is
-// rotated when |b_pq| > 2^-53 sqrt(|b_pp b_qq|) (relative accuracy) and
+// Before every sweep after the first, one launch scans each submatrix for an
+// entry that has to be rotated; a submatrix without one has converged and
+// the later kernels return at once for it.  A pair (p, q) is rotated when |b_pq| > 2^-53 sqrt(|b_pp b_qq|) (relative accuracy) and
 // |b_pq| > 256 * 2^-53 * ||B|| (rounding floor of the block products, with
 // ||B|| bounded by the Gershgorin interval of the full matrix).  Without the
 // floor, the rounding error of the MFMA block updates would keep rotating
@@ -106,22 +106,43 @@ __global__ void gather_windows(EighBatch e, const T* __restrict__ At, int64_t ld
     U[idx] = (r == c) ? 1.0 : 0.0;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    e.state[2 * p] = 0;      // done flag
-    e.state[2 * p + 1] = 0;  // rotations in current sweep
+    e.state[2 * p] = 0;      // last sweep that rotated (1-based)
+    e.state[2 * p + 1] = 1;  // last sweep to run: the first one always does
     e.stats[2 * p] = 0;      // sweep at which the submatrix was found converged
     e.stats[2 * p + 1] = 0;  // pair problems that needed rotations, all sweeps
   }
 }
 
-// Start of a sweep: a submatrix whose previous sweep needed no rotation is done.
-__global__ void sweep_begin(EighBatch e, int sweep) {
-  int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= e.P) return;
-  if (sweep > 0 && e.state[2 * p + 1] == 0 && !e.state[2 * p]) {
-    e.state[2 * p] = 1;
-    e.stats[2 * p] = sweep;
+__device__ inline bool sweep_active(const EighBatch& e, int p, int sweep) { return e.state[2 * p + 1] == sweep + 1; }
+
+// Whether the columns c0, c0 + step, ... of submatrix p hold an entry to
+// rotate (per thread; every entry above the diagonal, read where the pair
+// problems read it: along the columns of the symmetric B).
+__device__ inline int scan_columns(const EighBatch& e, int p, int c0, int step) {
+  const int Mp = e.Mp, M = e.wsize[p];
+  const double* B = e.Bw + (int64_t)p * Mp * Mp;
+  const double fl = noise_floor(e, p);
+  int need = 0;
+  for (int c = c0; c < M; c += step) {
+    const double* col = B + (int64_t)c * Mp;
+    const double dc = col[c];
+#pragma unroll 4
+    for (int r = c + 1 + (int)threadIdx.x; r < M; r += blockDim.x) {
+      const double v = col[r];
+      if (fabs(v) > fl && must_rotate(v, dc, B[r + (int64_t)r * Mp], fl)) need = 1;
+    }
   }
-  e.state[2 * p + 1] = 0;
+  return need;
+}
+
+// Start of sweep `sweep` > 0, gridDim.x workgroups per submatrix: it runs only
+// if the previous sweep ran, rotated, and left an entry to rotate.  (A sweep
+// that only confirmed this took 31 launches and 0.15 ms for 32 submatrices
+// of order 512.)
+__global__ __launch_bounds__(256) void sweep_scan(EighBatch e, int sweep) {
+  const int p = blockIdx.y;
+  if (!sweep_active(e, p, sweep - 1) || e.state[2 * p] != sweep) return;
+  if (scan_columns(e, p, blockIdx.x, gridDim.x)) atomicMax(&e.state[2 * p + 1], sweep + 1);
 }
 
 // ------------------------------------------------------------------ pair solve
@@ -200,11 +221,10 @@ struct SolveLds {
   double part[2][PS_W][32];  // partial inner products per slot, by round parity
   double nrm[4 * PS_W][B2];  // partial squared norms per column
 };
-// Pair problem k of submatrix p in the given round (PS_NT threads).
-__device__ void solve_pair(const EighBatch& e, int round, int p, int k, SolveLds& L) {
+// Pair problem k of submatrix p in the given round (PS_NT threads); whether it rotated.
+__device__ bool solve_pair(const EighBatch& e, int round, int p, int k, SolveLds& L) {
   const int npairs = e.nb / 2;
   int* flagR = flag_buf(e, round) + (int64_t)p * npairs + k;
-  if (e.state[2 * p]) { if (threadIdx.x == 0) *flagR = 0; return; }
   const int Mp = e.Mp;
   const int msize = e.wsize[p];
   int I, J;
@@ -246,7 +266,10 @@ __device__ void solve_pair(const EighBatch& e, int round, int p, int k, SolveLds
     test(B1[m], row0 + m, 62 - 2 * j, dr[m], dc[2]);
     test(B0[m], row0 + m, 63 - 2 * j, dr[m], dc[3]);
   }
-  if (!__syncthreads_or(need)) { if (threadIdx.x == 0) *flagR = 0; return; }
+  if (!__syncthreads_or(need)) {
+    if (threadIdx.x == 0) *flagR = 0;
+    return false;
+  }
   const double* sc = scal_of(e, p);
   const double sigma = 2.0 * fmax(fabs(sc[1]), fabs(sc[2])) + TINY;
   auto shift = [&](double v, int row, int col, int gcol) {
@@ -287,11 +310,11 @@ __device__ void solve_pair(const EighBatch& e, int round, int p, int k, SolveLds
   };
   const bool first = j == 0;
   auto move = [&](double& t0, double& b0, double& t1, double& b1) {
-    const double nt1 = dpp_d<DPP_FROM_RIGHT>(b1, t0), nb0 = dpp_d<DPP_FROM_LEFT>(t1, b1);
-    t0 = first ? t0 : t1;
+    const double nt0 = first ? t0 : t1, nb0 = dpp_d<DPP_FROM_LEFT>(t1, b1), nt1 = dpp_d<DPP_FROM_RIGHT>(b1, t0);
     b1 = b0;
-    t1 = nt1;
+    t0 = nt0;
     b0 = nb0;
+    t1 = nt1;
   };
   const double angle = e.angle > 0.0 ? e.angle : ANGLE;
   bool converged = false;
@@ -338,20 +361,15 @@ __device__ void solve_pair(const EighBatch& e, int round, int p, int k, SolveLds
       s0 = rot ? s0 : 0.0;
       // only rotations by more than the stopping angle keep the sweep going (see above)
       big |= __ballot(fabs(s0) > angle);
-      double x0 = 2.0 * c0 * s0 * ab, c1 = c0, s1 = s0, x1 = x0;
+      // the squared norms change by -+ tan t ab, 1 / cos t = ic
+      double x0 = rot ? s0 * ic * ab : 0.0, c1 = c0, s1 = s0, x1 = x0;
       swap32_d(c0, c1);
       swap32_d(s0, s1);
       swap32_d(x0, x1);
-      {
-        const double cc = c0 * c0, ss = s0 * s0, a = nT0, b = nB0;
-        nT0 = fma(cc, a, fma(ss, b, -x0));
-        nB0 = fma(ss, a, fma(cc, b, x0));
-      }
-      {
-        const double cc = c1 * c1, ss = s1 * s1, a = nT1, b = nB1;
-        nT1 = fma(cc, a, fma(ss, b, -x1));
-        nB1 = fma(ss, a, fma(cc, b, x1));
-      }
+      nT0 -= x0;
+      nB0 += x0;
+      nT1 -= x1;
+      nB1 += x1;
       move(nT0, nB0, nT1, nB1);
 #pragma unroll
       for (int m = 0; m < PS_R; ++m) {
@@ -384,15 +402,20 @@ __device__ void solve_pair(const EighBatch& e, int round, int p, int k, SolveLds
   }
   if (threadIdx.x == 0) {
     *flagR = 1;
-    atomicOr(&e.state[2 * p + 1], 1);
     atomicAdd(&e.stats[2 * p + 1], 1);
   }
+  return true;
 }
 
-__global__ __launch_bounds__(PS_NT) void pair_solve(EighBatch e, int round) {
+__device__ inline void solve_block(const EighBatch& e, int sweep, int round, int b, SolveLds& L) {
+  const int npairs = e.nb / 2, p = b / npairs;
+  if (!sweep_active(e, p, sweep)) return;
+  if (solve_pair(e, round, p, b % npairs, L) && threadIdx.x == 0) atomicMax(&e.state[2 * p], sweep + 1);
+}
+
+__global__ __launch_bounds__(PS_NT) void pair_solve(EighBatch e, int sweep) {
   __shared__ SolveLds L;
-  const int npairs = e.nb / 2;
-  solve_pair(e, round, blockIdx.x / npairs, blockIdx.x % npairs, L);
+  solve_block(e, sweep, 0, blockIdx.x, L);
 }
 
 // 64x64x64 products with FP64 MFMA by NTH / 64 waves: wave w owns rows
@@ -485,7 +508,6 @@ template <int NTH> __device__ inline void store_acc(double (*Z)[LS], v4d acc[2][
 // r + 1 read; the U tiles are read by nothing until the next round's U
 // update, so they run in the same launch as the next round's pair problems.
 template <int NTH> __device__ void apply_b_tile(const EighBatch& e, int round, int p, int w, double (*T)[LS]) {
-  if (e.state[2 * p]) return;
   const int npairs = e.nb / 2;
   const int Mp = e.Mp;
   const int* fl = flag_buf(e, round) + (int64_t)p * npairs;
@@ -543,7 +565,6 @@ template <int NTH> __device__ void apply_b_tile(const EighBatch& e, int round, i
 }
 
 template <int NTH> __device__ void apply_u_tile(const EighBatch& e, int round, int p, int ww, double (*T)[LS]) {
-  if (e.state[2 * p]) return;
   const int npairs = e.nb / 2;
   const int nrc = e.Mp / B2;
   const int Mp = e.Mp;
@@ -582,15 +603,15 @@ template <int NTH> __device__ void apply_u_tile(const EighBatch& e, int round, i
 
 // B tiles of a round: one eight-wave workgroup per tile (four fit a CU).
 constexpr int AB_NT = 512;
-__global__ __launch_bounds__(AB_NT) void pair_apply_b(EighBatch e, int round) {
+__global__ __launch_bounds__(AB_NT) void pair_apply_b(EighBatch e, int sweep, int round) {
   __shared__ double T[B2][LS];
-  const int npairs = e.nb / 2, ntri = npairs * (npairs + 1) / 2;
-  apply_b_tile<AB_NT>(e, round, blockIdx.x / ntri, blockIdx.x % ntri, T);
+  const int npairs = e.nb / 2, ntri = npairs * (npairs + 1) / 2, p = blockIdx.x / ntri;
+  if (sweep_active(e, p, sweep)) apply_b_tile<AB_NT>(e, round, p, blockIdx.x % ntri, T);
 }
 
 // The pair problems of round solve_round (the first P * npairs workgroups;
 // none when solve_round < 0) beside the U tiles of round u_round (the rest).
-__global__ __launch_bounds__(PS_NT) void pair_solve_apply_u(EighBatch e, int solve_round, int u_round) {
+__global__ __launch_bounds__(PS_NT) void pair_solve_apply_u(EighBatch e, int sweep, int solve_round, int u_round) {
   __shared__ union {
     SolveLds solve;
     double T[B2][LS];
@@ -599,10 +620,47 @@ __global__ __launch_bounds__(PS_NT) void pair_solve_apply_u(EighBatch e, int sol
   const int ns = solve_round >= 0 ? e.P * npairs : 0;
   const int b = blockIdx.x;
   if (b < ns) {
-    solve_pair(e, solve_round, b / npairs, b % npairs, L.solve);
+    solve_block(e, sweep, solve_round, b, L.solve);
   } else {
-    const int per = (e.Mp / B2) * npairs;
-    apply_u_tile<PS_NT>(e, u_round, (b - ns) / per, (b - ns) % per, L.T);
+    const int per = (e.Mp / B2) * npairs, p = (b - ns) / per;
+    if (sweep_active(e, p, sweep)) apply_u_tile<PS_NT>(e, u_round, p, (b - ns) % per, L.T);
+  }
+}
+
+// The sweeps from `sweep` on, one workgroup per submatrix doing all of its
+// tiles in turn: a single launch that returns at once in the usual case.  It
+// is some ten times slower per sweep than the launches above, so it stands
+// behind enough of those (see eigh_run) that only start vectors
+// far from any the method is meant for reach it.
+__global__ __launch_bounds__(PS_NT) void sweeps_left(EighBatch e, int sweep, int max_sweeps) {
+  __shared__ union {
+    SolveLds solve;
+    double T[B2][LS];
+  } L;
+  const int p = blockIdx.x, npairs = e.nb / 2;
+  if (!sweep_active(e, p, sweep - 1) || e.state[2 * p] != sweep) return;
+  int ran = sweep, rotated = sweep;
+  for (; sweep < max_sweeps && rotated == sweep; ++sweep) {
+    if (!__syncthreads_or(scan_columns(e, p, 0, 1))) break;
+    ran = sweep + 1;
+    for (int round = 0; round < e.nb - 1; ++round) {
+      for (int k = 0; k < npairs; ++k) {
+        if (solve_pair(e, round, p, k, L.solve)) rotated = sweep + 1;
+        __syncthreads();
+      }
+      for (int w = 0; w < npairs * (npairs + 1) / 2; ++w) {
+        apply_b_tile<PS_NT>(e, round, p, w, L.T);
+        __syncthreads();
+      }
+      for (int w = 0; w < (e.Mp / B2) * npairs; ++w) {
+        apply_u_tile<PS_NT>(e, round, p, w, L.T);
+        __syncthreads();
+      }
+    }
+  }
+  if (threadIdx.x == 0) {
+    e.state[2 * p] = rotated;
+    e.state[2 * p + 1] = ran;
   }
 }
 
@@ -611,7 +669,7 @@ __global__ __launch_bounds__(PS_NT) void pair_solve_apply_u(EighBatch e, int sol
 // [offset, offset + size) become start vectors X0 (zero outside the
 // submatrix rows) and shifts eps.  Ranking: one workgroup per 64 entries of a submatrix.
 constexpr int RS_NT = 64;  // entries ranked per workgroup (one per thread)
-__global__ __launch_bounds__(RS_NT) void rank_select(EighBatch e) {
+__global__ __launch_bounds__(RS_NT) void rank_select(EighBatch e, int max_sweeps) {
   const int p = blockIdx.x;
   const int Mp = e.Mp;
   const double* B = e.Bw + (int64_t)p * Mp * Mp;
@@ -625,10 +683,15 @@ __global__ __launch_bounds__(RS_NT) void rank_select(EighBatch e) {
   int rank = 0;
   for (int j = 0; j < Mp; ++j) rank += order_before(dsh[j], j, di, i);
   sel[rank] = i;  // rank -> local index; ranks are a permutation even with NaN
-  // not converged: the last sweep still rotated and no sweep was rotation-free
-  int* inf = info_of(e, p);
-  if (blockIdx.y == 0 && threadIdx.x == 0 && e.state[2 * p] == 0 && e.state[2 * p + 1] != 0 && inf)
-    atomicCAS(inf, 0, PFSM_INFO_EIGH_NOCONV);
+  // ran: the last sweep that ran; after it nothing was left to rotate, unless
+  // it rotated and was the last allowed one: not converged
+  if (blockIdx.y == 0 && threadIdx.x == 0) {
+    int* inf = info_of(e, p);
+    const int ran = e.state[2 * p + 1], rotated = e.state[2 * p] == ran;
+    if (!rotated) e.stats[2 * p] = ran;
+    else if (ran < max_sweeps) e.stats[2 * p] = ran + 1;
+    else if (inf) atomicCAS(inf, 0, PFSM_INFO_EIGH_NOCONV);
+  }
 }
 
 template <typename T>
@@ -666,19 +729,28 @@ static hipError_t eigh_run(const EighBatch& e, const T* At, int64_t ldat, int ma
     dim3 grid((unsigned)std::min<int64_t>(((int64_t)e.Mp * e.Mp + 255) / 256, 1024), e.P);
     hipLaunchKernelGGL(gather_windows<T>, grid, dim3(256), 0, s, e, At, ldat);
   }
-  for (int sw = 0; sw < max_sweeps; ++sw) {
-    hipLaunchKernelGGL(sweep_begin, dim3((e.P + 63) / 64), dim3(64), 0, s, e, sw);
+  // Sweeps with one launch per round and kind of tile; launches of the sweeps
+  // that a submatrix does not need cost about 2.4 us each (31 per sweep at
+  // order 512), so only a margin over the usual count is enqueued this way: a
+  // basis close to the eigenvectors takes one active sweep to the mixed path's
+  // floor and two to the FP64 one, a single submatrix (a full diagonalisation
+  // from any basis) about ten.
+  const int spread = std::min(max_sweeps, e.P == 1 ? 16 : e.floor_rel > 0.0 ? 4 : 6);
+  for (int sw = 0; sw < spread; ++sw) {
+    if (sw > 0) hipLaunchKernelGGL(sweep_scan, dim3(std::min(e.Mp, 64), e.P), dim3(256), 0, s, e, sw);
     // round r: B tiles, then the next round's pair problems beside the U tiles
     const int rounds = e.nb - 1;
-    hipLaunchKernelGGL(pair_solve, dim3(e.P * npairs), dim3(PS_NT), 0, s, e, 0);
+    hipLaunchKernelGGL(pair_solve, dim3(e.P * npairs), dim3(PS_NT), 0, s, e, sw);
     for (int r = 0; r < rounds; ++r) {
-      hipLaunchKernelGGL(pair_apply_b, dim3(e.P * (npairs * (npairs + 1) / 2)), dim3(AB_NT), 0, s, e, r);
+      hipLaunchKernelGGL(pair_apply_b, dim3(e.P * (npairs * (npairs + 1) / 2)), dim3(AB_NT), 0, s, e, sw, r);
       const int next = r + 1 < rounds ? r + 1 : -1;
       const unsigned grid = (unsigned)((next >= 0 ? e.P * npairs : 0) + e.P * nrc * npairs);
-      hipLaunchKernelGGL(pair_solve_apply_u, dim3(grid), dim3(PS_NT), 0, s, e, next, r);
+      hipLaunchKernelGGL(pair_solve_apply_u, dim3(grid), dim3(PS_NT), 0, s, e, sw, next, r);
     }
   }
-  hipLaunchKernelGGL(rank_select, dim3(e.P, e.Mp / RS_NT), dim3(RS_NT), e.Mp * sizeof(double), s, e);
+  if (spread < max_sweeps)
+    hipLaunchKernelGGL(sweeps_left, dim3(e.P), dim3(PS_NT), 0, s, e, spread, max_sweeps);
+  hipLaunchKernelGGL(rank_select, dim3(e.P, e.Mp / RS_NT), dim3(RS_NT), e.Mp * sizeof(double), s, e, max_sweeps);
   return hipGetLastError();
 }
 

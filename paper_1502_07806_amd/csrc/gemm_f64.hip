@@ -609,7 +609,7 @@ int gemm_f64_tile(int64_t M, int64_t N, bool lower) {
   auto filled = [&](int64_t t) { return (double)t / (double)(CUS * ((t + CUS - 1) / CUS)); };
   const int64_t t128 = tiles(128), t64 = tiles(64);
   if (t64 <= 100) return 32;
-  return filled(t128) >= 0.94 * filled(t64) ? 128 : 64;
+  return filled(t128) >= 0.9 * filled(t64) ? 128 : 64;
 }
 
 template <bool TA, bool TB>

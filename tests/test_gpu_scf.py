@@ -74,6 +74,30 @@ def test_full_diag_equal_diagonal(pf, n):
     assert np.max(np.abs(A @ V - V * lam)) <= 1e-12
 
 
+@pytest.mark.parametrize("n,precision,tol", [(130, "fp64", 1e-12), (200, "fp64", 1e-12), (200, "mixed_bf16", 1e-8)])
+def test_late_sweeps(pf, n, precision, tol):
+    """Submatrices that need more sweeps than are enqueued round by round (two
+    windows, each the whole of a dense random matrix in the identity basis):
+    the single launch that finishes them gives the eigenpairs of the matrix.
+    FP64 tolerance as above (norm about 2 sqrt(n)); mixed: its bar."""
+    dev = torch.device("cuda:0")
+    A = _random_symmetric(n, 7 * n) / np.sqrt(n)
+    plan = pf.Plan(n, [0, n // 2, n], halo=n, iterations=0, precision=precision)
+    lam, V = plan.solve(torch.from_numpy(A).to(dev), torch.eye(n, dtype=torch.float64, device=dev))
+    spread = 6 if precision == "fp64" else 4
+    assert min(plan.debug_stats()["converged_sweep"]) > spread  # past the sweeps with their own launches
+    lam, V = lam.cpu().numpy(), V.cpu().numpy()
+    assert np.max(np.abs(lam - np.linalg.eigvalsh(A))) <= tol
+    if precision == "fp64":
+        assert np.max(np.abs(V.T @ V - np.eye(n))) <= tol
+        assert np.max(np.abs(A @ V - V * lam)) <= tol
+    # the limit just below the last active sweep is reported
+    conv = max(plan.debug_stats()["converged_sweep"])
+    short = pf.Plan(n, [0, n // 2, n], halo=n, iterations=0, precision=precision, max_sweeps=conv - 1)
+    short.solve(torch.from_numpy(A).to(dev), torch.eye(n, dtype=torch.float64, device=dev), check=False)
+    assert int(short.info.item()) == -3
+
+
 def test_scf_sequence_switches_to_pfsm(pf):
     dev = torch.device("cuda:0")
     n = 1024
