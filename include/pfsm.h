@@ -278,7 +278,10 @@ pfsm_status pfsm_diagnostics(pfsm_plan* plan, const double* dA, int64_t lda, con
  * the elapsed milliseconds between boundary k and k+1 to ms[s * (PFSM_TIMING_BOUNDS-1) + k]
  * (unused stages read 0).  Stage order: 0 basis change, 1 step length, 2
  * submatrix eigensolver + start vectors, 3 + 2i shifted product of iteration i,
- * 4 + 2i folded-spectrum update of iteration i (i < iterations, at most 8),
+ * 4 + 2i folded-spectrum update of iteration i (i < iterations, at most 8;
+ * where the FP64 path applies all iterations as one polynomial of At, the
+ * products with the start vectors and the powers of At fall in the first
+ * shifted stage, the remaining whole products in the last update stage),
  * 19 overlap, 20 Cholesky-QR, 21 Rayleigh quotients, 22 ordering, 23
  * back-rotation (mixed precision: with the digit split of A and V_new), 24
  * refinement product Z = A V_new (mixed precision, one launch), 25

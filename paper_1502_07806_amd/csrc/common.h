@@ -26,6 +26,8 @@ enum GemmEpi : int {
   EPI_FSUPD = 2,   // C = D(i,j) - a * (acc - B(i,j)*eps[j]), a = *alpha_dev or alpha
   EPI_RQ = 3,      // part[tile_m][j] = sum_{i in tile} acc(i,j) * D(i,j)   (C untouched); and
                    // part2[tile_m][j] = sum_{i in tile} acc(i,j)^2 when part2 is set
+  EPI_POLY = 5,    // poly[o] = (poly_init[o] ? poly_init[o][j] * B(i,j) : poly[o]) + poly_coef[o][j] * acc for
+                   // o < poly_count (coefficient 1 where poly_coef[o] is null); C is not written
   EPI_G2S = 4,     // C = B(i,j) + eps[i] * (D(i,j) - acc); part[tile_m][j] = sum_i (D(i,j) - acc)^2
                    // when part is set (B square operand, not transposed; C must not alias B)
 };
@@ -45,6 +47,10 @@ struct GemmArgs {
   const int32_t* krange;     // optional [tiles_n][2] K range per column tile
   int lower_only;            // skip tiles strictly above the diagonal; RQ: A is symmetric, only its blocks on
                              // and below the diagonal are read (not with part2)
+  int poly_count;            // EPI_POLY outputs (at most 3; ld = ldc)
+  double* poly[3];
+  const double* poly_coef[3];
+  const double* poly_init[3];
   int in_place;              // C aliases A: N must fit one column tile (N <= 64)
 };
 

@@ -206,6 +206,37 @@ __device__ inline void f64_epilogue(const GemmArgs& g, v4d (&acc)[WI][WJ], int64
     return;
   }
 
+  if (EPI == EPI_POLY) {
+    // one output at a time; the loads of one row block are gathered before its stores
+    for (int o = 0; o < g.poly_count; ++o) {
+      double* P = g.poly[o];
+      const double *ci = g.poly_init[o], *cc = g.poly_coef[o];
+      const double* src = ci ? g.B : P;
+      const int64_t lds = ci ? g.ldb : g.ldc;
+#pragma unroll
+      for (int ib = 0; ib < WI; ++ib) {
+        const int64_t gi = m0 + wi0 + ib * 16 + l16;
+        if (gi >= g.M) continue;
+        double v[WJ][4];
+#pragma unroll
+        for (int jb = 0; jb < WJ; ++jb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int64_t c = n0 + wj0 + jb * 16 + lq + 4 * r, gj = c < g.N ? c : g.N - 1;
+            v[jb][r] = (ci ? ci[gj] : 1.0) * src[gi + gj * lds] + (cc ? cc[gj] : 1.0) * acc[ib][jb][r];
+          }
+#pragma unroll
+        for (int jb = 0; jb < WJ; ++jb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int64_t gj = n0 + wj0 + jb * 16 + lq + 4 * r;
+            if (gj < g.N) P[gi + gj * g.ldc] = v[jb][r];
+          }
+      }
+    }
+    return;
+  }
+
   double a_eff = g.alpha;
   if (EPI == EPI_FSUPD && g.alpha_dev) a_eff = *g.alpha_dev;
 #pragma unroll
@@ -560,6 +591,7 @@ hipError_t launch_epi(int epi, const GemmArgs& a, hipStream_t s) {
     F64_CASE(EPI_FSUPD)
     F64_CASE(EPI_RQ)
     F64_CASE(EPI_G2S)
+    F64_CASE(EPI_POLY)
 #undef F64_CASE
     default: return hipErrorInvalidValue;
   }
@@ -585,6 +617,7 @@ hipError_t launch_dl(int epi, const GemmArgs& a, hipStream_t s) {
     F64_CASE(EPI_FSUPD)
     F64_CASE(EPI_RQ)
     F64_CASE(EPI_G2S)
+    F64_CASE(EPI_POLY)
 #undef F64_CASE
     default: return hipErrorInvalidValue;
   }
@@ -632,8 +665,8 @@ hipError_t launch_tile(int epi, const GemmArgs& a, hipStream_t s) {
 }
 
 hipError_t gemm_f64(bool ta, bool tb, int epi, const GemmArgs& a, hipStream_t s) {
-  // SHIFT / FSUPD read B at output positions: only the non-transposed square case is valid.
-  if ((epi == EPI_SHIFT || epi == EPI_FSUPD || epi == EPI_G2S) && (tb || a.K < a.M)) return hipErrorInvalidValue;
+  // SHIFT / FSUPD / G2S / POLY read B at output positions: only the non-transposed square case is valid.
+  if ((epi == EPI_SHIFT || epi == EPI_FSUPD || epi == EPI_G2S || epi == EPI_POLY) && (tb || a.K < a.M)) return hipErrorInvalidValue;
   if (!ta && !tb) return launch_tile<false, false>(epi, a, s);
   if (ta && !tb) return launch_tile<true, false>(epi, a, s);
   if (!ta && tb) return launch_tile<false, true>(epi, a, s);

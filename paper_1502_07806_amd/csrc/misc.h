@@ -17,6 +17,16 @@ hipError_t gershgorin_alpha(const double* At, int64_t n, int64_t ld, int q, doub
 // The same from FP32 columns (each entry widened exactly to FP64).
 hipError_t gershgorin_alpha(const float* At, int64_t n, int64_t ld, int q, double user_alpha,
                             double* part_lo, double* part_hi, double* scal, int* info, hipStream_t s);
+// Folded-spectrum polynomial of the iteration x <- x - alpha (A - eps)^q x taken
+// `iterations` times, about c = the middle of scal's Gershgorin interval:
+// coef[k n + j] = coefficient of (A - c)^k in (1 - alpha (A - eps_j)^q)^iterations,
+// k = 0 .. q iterations <= FS_POLY_MAX_DEGREE.
+constexpr int FS_POLY_MAX_DEGREE = 8;
+hipError_t fs_poly_coefs(const double* eps, const double* scal, int64_t n, int q, int iterations, double* coef,
+                         hipStream_t s);
+// Diagonal of A (ld = n): saved to keep and replaced by itself minus c (center
+// set), or put back from keep.
+hipError_t center_diag(double* A, int64_t n, double* keep, const double* scal, int center, hipStream_t s);
 hipError_t rq_reduce(const double* part, int tiles_m, int64_t n, const double* den, double* out, hipStream_t s);
 hipError_t col_norm2(const double* X, int64_t m, int64_t n, int64_t ldx, double* out, hipStream_t s);
 hipError_t finalize_order(const double* lam_u, const double* X, int64_t n, int64_t ldx, double* Xp, int64_t ldxp,

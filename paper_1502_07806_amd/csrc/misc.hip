@@ -89,6 +89,39 @@ __global__ __launch_bounds__(NT) void k_gersh_final(const double* lo, const doub
   }
 }
 
+__device__ inline double gersh_mid(const double* scal) { return 0.5 * (scal[1] + scal[2]); }
+
+__global__ __launch_bounds__(NT) void k_fs_poly(const double* eps, const double* scal, int64_t n, int q,
+                                                int iterations, double* coef) {
+  const int64_t j = (int64_t)blockIdx.x * NT + threadIdx.x;
+  if (j >= n) return;
+  const double a = scal[0], e = eps[j] - gersh_mid(scal);
+  const double b0 = q == 2 ? 1.0 - a * e * e : 1.0 + a * e, b1 = q == 2 ? 2.0 * a * e : -a, b2 = q == 2 ? -a : 0.0;
+  double p[FS_POLY_MAX_DEGREE + 1];
+#pragma unroll
+  for (int k = 0; k <= FS_POLY_MAX_DEGREE; ++k) p[k] = k == 0 ? 1.0 : 0.0;
+  for (int it = 0; it < iterations; ++it)
+#pragma unroll
+    for (int k = FS_POLY_MAX_DEGREE; k >= 0; --k)
+      p[k] = b0 * p[k] + (k >= 1 ? b1 * p[k - 1] : 0.0) + (k >= 2 ? b2 * p[k - 2] : 0.0);
+#pragma unroll
+  for (int k = 0; k <= FS_POLY_MAX_DEGREE; ++k)
+    if (k <= q * iterations) coef[(int64_t)k * n + j] = p[k];
+}
+
+__global__ __launch_bounds__(NT) void k_center_diag(double* A, int64_t n, double* keep, const double* scal,
+                                                    int center) {
+  const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+  if (i >= n) return;
+  double* d = A + i * (n + 1);
+  if (center) {
+    keep[i] = *d;
+    *d -= gersh_mid(scal);
+  } else {
+    *d = keep[i];
+  }
+}
+
 __global__ void k_rq_reduce(const double* part, int tiles_m, int64_t n, const double* den, double* out) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
@@ -385,6 +418,18 @@ hipError_t gershgorin_alpha(const double* At, int64_t n, int64_t ld, int q, doub
 hipError_t gershgorin_alpha(const float* At, int64_t n, int64_t ld, int q, double user_alpha, double* part_lo,
                             double* part_hi, double* scal, int* info, hipStream_t s) {
   return gershgorin_alpha_t(At, n, ld, q, user_alpha, part_lo, part_hi, scal, info, s);
+}
+
+hipError_t fs_poly_coefs(const double* eps, const double* scal, int64_t n, int q, int iterations, double* coef,
+                         hipStream_t s) {
+  if (q * iterations > FS_POLY_MAX_DEGREE) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_fs_poly, dim3((unsigned)((n + NT - 1) / NT)), dim3(NT), 0, s, eps, scal, n, q, iterations, coef);
+  return hipGetLastError();
+}
+
+hipError_t center_diag(double* A, int64_t n, double* keep, const double* scal, int center, hipStream_t s) {
+  hipLaunchKernelGGL(k_center_diag, dim3((unsigned)((n + NT - 1) / NT)), dim3(NT), 0, s, A, n, keep, scal, center);
+  return hipGetLastError();
 }
 
 hipError_t rq_reduce(const double* part, int tiles_m, int64_t n, const double* den, double* out, hipStream_t s) {

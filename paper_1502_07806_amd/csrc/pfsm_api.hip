@@ -83,6 +83,9 @@ struct pfsm_plan {
   size_t m_split = 0, split_bytes = 0;  // K-split scratch of the lower-triangle split-BF16 products
   size_t m_gate = 0, m_bcopy = 0;  // orthonormalisation: fallback gate word, Cholesky block copies
   size_t m_Epk = 0, m_fm = 0;       // band form of the folded-spectrum products: off-diagonal At, far maxima
+  // FP64 path: folded-spectrum iterations as one polynomial (0: step by step)
+  int poly_block = 0;               // s: powers of At up to s, blocks of s coefficients
+  size_t p_mat = 0, p_coef = 0, p_diag = 0;  // powers and blocks (n x n each), coefficients, diagonal of At
   size_t m_gcl = 0;                 // gate scalars of the orthonormalisation correction's band form
 };
 
@@ -157,6 +160,39 @@ bool mixed_band_form(const pfsm_plan* pl) {
 double eigh_floor(const pfsm_plan* pl) { return pl->precision == PFSM_PREC_MIXED_BF16 ? EIGH_FLOOR_MIXED : 0.0; }
 // Stopping rotation of the pair problems: looser with the looser floor.
 double eigh_angle(const pfsm_plan* pl) { return pl->precision == PFSM_PREC_MIXED_BF16 ? EIGH_ANGLE_MIXED : 0.0; }
+
+// The folded-spectrum iterations with fixed shifts are one polynomial of At per
+// column, (1 - alpha (At - eps_j)^q)^iterations of degree D = q iterations,
+// applied to start vectors that are zero outside their submatrix rows.  With
+// the powers M_k = (At - c)^k, k <= s, and Horner's rule in blocks of s
+// coefficients, every product with a power M_k, k >= 1, of the start vectors
+// runs over the submatrix rows only, the powers are symmetric (half a
+// product each), and ceil(D / s) - 1 whole products are left instead of
+// D - 1.  c is the middle of the Gershgorin interval, so that with the
+// automatic step length 1 / rho^q the terms' magnitudes sum to at most
+// 2^iterations (a caller's step length has no such bound, and more than four
+// iterations lose more than four bits: those go step by step).  At N = 8192,
+// three iterations of Eq. 11, submatrices of 512: 31 ms instead of 77; the
+// 14 launches instead of 6 pay from n = 512 (0.86 against 1.56 ms at 2048).
+// Returns s, or 0: step by step.
+int fs_poly_block(const pfsm_plan* pl) {
+  const int D = pl->q * pl->iterations;
+  if (pl->precision != PFSM_PREC_FP64 || pl->shift_mode != PFSM_SHIFT_FIXED || pl->alpha > 0.0) return 0;
+  if (pl->iterations < 1 || pl->iterations > 4 || D < 2 || pl->n < 512) return 0;
+  double rows = 0.0;  // mean K range of a column tile, in units of n
+  for (size_t t = 0; t + 1 < pl->krange.size(); t += 2) rows += pl->krange[t + 1] - pl->krange[t];
+  rows /= (double)pl->n * (double)(pl->krange.size() / 2);
+  const int s = D == 2 || D == 4 ? 2 : 3;
+  const double steps = rows + (D - 1);
+  const double poly = 0.55 * (s - 1) + rows * s + ((D + s - 1) / s - 1);
+  return poly < 0.85 * steps ? s : 0;
+}
+// Matrices of the polynomial form beyond At and the two work buffers: the
+// powers 2 .. s and the blocks after the first.
+size_t fs_poly_matrices(const pfsm_plan* pl) {
+  const int D = pl->q * pl->iterations, s = pl->poly_block;
+  return (size_t)(s - 1) + (size_t)((D + s - 1) / s - 1);
+}
 
 // Submatrix eigensolver arguments: every pointer into the plan's workspace layout.
 EighBatch eigh_batch(const pfsm_plan* pl, char* W, int* info, const double* scal) {
@@ -393,6 +429,18 @@ pfsm_status pfsm_plan_create(pfsm_plan** out, const pfsm_desc* d) {
     pl->m_fm = w; w = align256(w + (size_t)(2 * pl->iterations + 4) * sizeof(unsigned));
     pl->m_gcl = w; w = align256(w + 2 * sizeof(double));
   }
+  pl->poly_block = fs_poly_block(pl);
+  if (pl->poly_block) {
+    const size_t before = w;
+    pl->p_mat = w; w = align256(w + fs_poly_matrices(pl) * N2);
+    pl->p_coef = w; w = align256(w + (size_t)(pl->q * pl->iterations + 1) * n * sizeof(double));
+    pl->p_diag = w; w = align256(w + n * sizeof(double));
+    // a plan that fits the library's own workspace keeps fitting it
+    if (before <= (size_t)PFSM_STATIC_SCRATCH_BYTES && w > (size_t)PFSM_STATIC_SCRATCH_BYTES) {
+      pl->poly_block = 0;
+      w = before;
+    }
+  }
   pl->total = w;
   *out = pl;
   return PFSM_OK;
@@ -536,8 +584,51 @@ static pfsm_status solve_fp64(pfsm_plan* pl, const double* dA, int64_t lda, cons
   PFSM_TRY(embed_start_vectors(e, X, n, eps, n, s));
   clk.mark(3);
 
-  // (5) folded-spectrum iterations.
-  for (int it = 0; it < pl->iterations; ++it) {
+  // (5) folded-spectrum iterations, as one polynomial of At (see fs_poly_block) ...
+  if (pl->poly_block) {
+    const int ps = pl->poly_block, D = pl->q * pl->iterations, blocks = (D + ps - 1) / ps;
+    double* coef = (double*)(W + pl->p_coef);
+    double* mat = (double*)(W + pl->p_mat);
+    const size_t n2 = (size_t)n * n;
+    const double* M[4] = {nullptr, At, mat, mat + n2};  // powers 1 .. ps of At - c
+    double* blk[4] = {Wt, mat + (ps - 1) * n2, mat + ps * n2, mat + (ps + 1) * n2};
+    PFSM_TRY(fs_poly_coefs(eps, scal, n, pl->q, pl->iterations, coef, s));
+    PFSM_TRY(center_diag(At, n, (double*)(W + pl->p_diag), scal, 1, s));
+    for (int k = 2; k <= ps; ++k) {  // M_k = M_1 M_(k-1), symmetric
+      GemmArgs g = {};
+      g.M = n; g.N = n; g.K = n; g.A = At; g.lda = n; g.B = M[k - 1]; g.ldb = n; g.C = (double*)M[k]; g.ldc = n;
+      g.alpha = 1.0; g.lower_only = 1;
+      PFSM_TRY(gemm_f64(true, false, EPI_STORE, g, s));
+      PFSM_TRY(mirror_lower((double*)M[k], n, n, s));
+    }
+    // blk[b] = sum over its coefficients c_(ps b + k) M_k X0 (the last block's up to c_D)
+    for (int k = 1; k <= ps; ++k) {
+      GemmArgs g = {};
+      g.M = n; g.N = n; g.K = n; g.A = M[k]; g.lda = n; g.B = X; g.ldb = n; g.ldc = n; g.krange = pl->d_krange;
+      for (int b = 0; b < blocks; ++b) {
+        if (ps * b + k > D || (k == ps && b + 1 < blocks)) continue;
+        g.poly[g.poly_count] = blk[b];
+        g.poly_coef[g.poly_count] = coef + (int64_t)(ps * b + k) * n;
+        g.poly_init[g.poly_count] = k == 1 ? coef + (int64_t)(ps * b) * n : nullptr;
+        ++g.poly_count;
+      }
+      if (g.poly_count) PFSM_TRY(gemm_f64(true, false, EPI_POLY, g, s));
+    }
+    for (int it = 0; it < pl->iterations && it < 8; ++it) clk.mark(4 + 2 * it);
+    // Horner's rule: the whole products, all in the last iteration's update stage
+    for (int b = blocks - 2; b >= 0; --b) {
+      GemmArgs g = {};
+      g.M = n; g.N = n; g.K = n; g.A = M[ps]; g.lda = n; g.B = blk[b + 1]; g.ldb = n; g.ldc = n;
+      g.poly_count = 1;
+      g.poly[0] = blk[b];
+      PFSM_TRY(gemm_f64(true, false, EPI_POLY, g, s));
+    }
+    if (pl->iterations <= 8) clk.mark(3 + 2 * pl->iterations);
+    PFSM_TRY(center_diag(At, n, (double*)(W + pl->p_diag), scal, 0, s));
+    std::swap(X, Wt);
+  }
+  // ... or step by step.
+  for (int it = 0; it < pl->iterations && !pl->poly_block; ++it) {
     const int32_t* kr = (it == 0 && pl->shift_mode == PFSM_SHIFT_FIXED) ? pl->d_krange : nullptr;
     if (pl->shift_mode == PFSM_SHIFT_RAYLEIGH) {
       GemmArgs r = {};

@@ -88,6 +88,21 @@ def test_options(pf, kw):
     _compare(lam, Vo, lam_ref, V_ref, A)
 
 
+@pytest.mark.parametrize("q,iterations,shift", [(2, 1, 0.0), (2, 2, 0.0), (2, 3, 0.0), (2, 3, 50.0), (2, 4, 0.0),
+                                                (1, 2, 0.0), (1, 3, -50.0), (1, 4, 0.0)])
+def test_fs_polynomial(pf, q, iterations, shift):
+    """Every degree of the polynomial form of the folded-spectrum iterations
+    (odd order, ragged slices), also with the spectrum far from zero, against
+    the oracle's step-by-step iterations."""
+    n, offs, halo = 601, uniform_layout(601, 90), 45
+    A, V, _, _ = prescribed_problem(n, n // 2, 1e-2, 6100 + 10 * q + iterations)
+    A, V = A.numpy() + shift * np.eye(n), V.numpy()
+    lam_ref, V_ref, info_ref = pfsm_ref(A, V, offs, halo, iterations, q)
+    _, info, lam, Vo = _run(pf, A, V, offs, halo, iterations=iterations, fs_power=q)
+    assert info == info_ref == 0
+    _compare(lam, Vo, lam_ref, V_ref, A)
+
+
 def test_single_full_window_matches_jacobi(pf):
     A, V, lam_ex, _ = prescribed_problem(192, 96, 1e-2, 55)
     A, V = A.numpy(), V.numpy()
