@@ -221,8 +221,212 @@ struct SolveLds {
   double part[2][PS_W][32];  // partial inner products per slot, by round parity
   double nrm[4 * PS_W][B2];  // partial squared norms per column
 };
-// Pair problem k of submatrix p in the given round (PS_NT threads); whether it rotated.
-__device__ bool solve_pair(const EighBatch& e, int round, int p, int k, SolveLds& L) {
+// Pair problems whose first-order rotations are all small (a basis close to
+// the eigenvectors, and the last sweeps from any basis), FP64 path: Newton's
+// iteration on the whole eigenvector matrix X of S (Ogita and Aishima's
+// refinement).  With R = I - X^T X and St = X^T S X,
+//   E_ij = R_ij / 2 + (St_ij + (l_i + l_j) R_ij / 2) / (l_j - l_i),
+//   E_ii = R_ii / 2,  X <- X + X E
+// squares the error of X.  The second term is formed from the same symmetric
+// St_ij for (i, j) and (j, i) and so is exactly antisymmetric: rounding
+// differences of St over a small gap would otherwise tilt the columns.  From
+// X = I the first step needs no product (E_ij = S_ij / (S_jj - S_ii)), each further one four 64 x 64 products on the
+// matrix cores.  It ends after a step with every |E_ij| <= 2^-30, whose square
+// is below the rounding.  A pair closer than its coupling allows (|E_ij| >
+// 2^-8) is left unrotated when the coupling lies below the rotation floor, as
+// the sweeps' own test leaves it; otherwise, and when five steps do not do, the
+// result is false and the Jacobi sweeps take over.  About 12 us for one
+// product step against 33 us for each Jacobi sweep of the 64 x 64 problem.
+constexpr double NEWTON_MAX = 0.00390625;            // 2^-8
+constexpr double NEWTON_DONE = 9.313225746154785e-10;  // 2^-30
+constexpr int NEWTON_STEPS = 5;
+struct NewtonLds {
+  double X[B2][LS];
+  double Y[B2][LS];
+  double lam[B2];
+};
+__device__ bool newton_pair(const double* B, int Mp, int I, int J, double fl, double* Rg, NewtonLds& L) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l16 = lane & 15, lq = lane >> 4;
+  const int i0 = (wave & 1) * 32, j0 = (wave >> 1) * 32;  // this wave's quadrant
+  // element (ib, jb, r) of a product: row i0 + 16 ib + l16, column j0 + 16 jb + lq + 4 r
+  auto row = [&](int ib) { return i0 + 16 * ib + l16; };
+  auto col = [&](int jb, int r) { return j0 + 16 * jb + lq + 4 * r; };
+  v4d st[2][2], xx[2][2];
+  const auto clear = [](v4d (&a)[2][2]) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) a[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
+  };
+  if (threadIdx.x < B2) L.lam[threadIdx.x] = B[pair_idx(threadIdx.x, I, J) * (int64_t)(Mp + 1)];
+  for (int step = 0; step < NEWTON_STEPS; ++step) {
+    if (step == 0) {
+#pragma unroll
+      for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int i = max(row(ib), col(jb, r)), j = min(row(ib), col(jb, r));  // one triangle for both
+            st[ib][jb][r] = B[pair_idx(i, I, J) + (int64_t)pair_idx(j, I, J) * Mp];
+            xx[ib][jb][r] = i == j ? 1.0 : 0.0;
+          }
+    } else {
+      // Y = S X: S from memory (symmetric, its columns), X from LDS
+      double af[B2 / 4][2];
+#pragma unroll
+      for (int kk = 0; kk < B2 / 4; ++kk)
+#pragma unroll
+        for (int ib = 0; ib < 2; ++ib)
+          af[kk][ib] = B[pair_idx(row(ib), I, J) + (int64_t)pair_idx(4 * kk + lq, I, J) * Mp];
+      clear(st);
+#pragma unroll
+      for (int kk = 0; kk < B2 / 4; ++kk) {
+        double bf[2];
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb) bf[jb] = L.X[4 * kk + lq][j0 + 16 * jb + l16];
+#pragma unroll
+        for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+          for (int jb = 0; jb < 2; ++jb)
+            st[ib][jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(bf[jb], af[kk][ib], st[ib][jb], 0, 0, 0);
+      }
+#pragma unroll
+      for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) L.Y[row(ib)][col(jb, r)] = st[ib][jb][r];
+      __syncthreads();
+      // X^T X and St = X^T Y
+      clear(st);
+      clear(xx);
+#pragma unroll
+      for (int kk = 0; kk < B2 / 4; ++kk) {
+        double a2[2], bx[2], by[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          a2[u] = L.X[4 * kk + lq][row(u)];
+          bx[u] = L.X[4 * kk + lq][j0 + 16 * u + l16];
+          by[u] = L.Y[4 * kk + lq][j0 + 16 * u + l16];
+        }
+#pragma unroll
+        for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+          for (int jb = 0; jb < 2; ++jb) {
+            xx[ib][jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(bx[jb], a2[ib], xx[ib][jb], 0, 0, 0);
+            st[ib][jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(by[jb], a2[ib], st[ib][jb], 0, 0, 0);
+          }
+      }
+#pragma unroll
+      for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (row(ib) == col(jb, r)) L.lam[row(ib)] = st[ib][jb][r] / xx[ib][jb][r];
+      __syncthreads();  // every wave has read Y
+#pragma unroll
+      for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) L.Y[row(ib)][col(jb, r)] = st[ib][jb][r];
+      __syncthreads();
+#pragma unroll
+      for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) st[ib][jb][r] = 0.5 * (st[ib][jb][r] + L.Y[col(jb, r)][row(ib)]);
+    }
+    __syncthreads();
+    int flags = 0;  // 1: not done after this step, 2: not for this iteration
+#pragma unroll
+    for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+      for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = row(ib), j = col(jb, r);
+          const double rij = (i == j ? 1.0 : 0.0) - xx[ib][jb][r];
+          double v = 0.5 * rij;
+          if (i != j) {
+            const double num = fma(0.5 * (L.lam[i] + L.lam[j]), rij, st[ib][jb][r]), gap = L.lam[j] - L.lam[i];
+            if (fabs(num) <= NEWTON_MAX * fabs(gap)) v += num == 0.0 ? 0.0 : num / gap;
+            else if (!(fabs(num) <= fl)) flags |= 2;
+            if (fabs(v) > NEWTON_DONE) flags |= 1;
+          }
+          st[ib][jb][r] = v;
+        }
+    if (__syncthreads_or(flags & 2)) return false;
+    const bool more = __syncthreads_or(flags & 1);
+    if (more && step + 1 == NEWTON_STEPS) return false;
+    if (step == 0) {
+#pragma unroll
+      for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) L.X[row(ib)][col(jb, r)] = (row(ib) == col(jb, r) ? 1.0 : 0.0) + st[ib][jb][r];
+    } else {
+#pragma unroll
+      for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) L.Y[row(ib)][col(jb, r)] = st[ib][jb][r];
+      __syncthreads();
+      clear(st);
+#pragma unroll
+      for (int kk = 0; kk < B2 / 4; ++kk) {
+        double a2[2], b2[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          a2[u] = L.X[row(u)][4 * kk + lq];
+          b2[u] = L.Y[4 * kk + lq][j0 + 16 * u + l16];
+        }
+#pragma unroll
+        for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+          for (int jb = 0; jb < 2; ++jb)
+            st[ib][jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(b2[jb], a2[ib], st[ib][jb], 0, 0, 0);
+      }
+      __syncthreads();  // every wave has read X
+#pragma unroll
+      for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) L.X[row(ib)][col(jb, r)] += st[ib][jb][r];
+    }
+    __syncthreads();
+    if (!more) break;
+  }
+  for (int idx = threadIdx.x; idx < B2 * B2; idx += PS_NT) Rg[idx] = L.X[idx / B2][idx % B2];
+  return true;
+}
+
+// LDS of a pair problem: the Jacobi sweeps', or Newton's.
+template <bool NEWTON> struct PairLds {
+  SolveLds jacobi;
+  __device__ NewtonLds& newton() { return *(NewtonLds*)nullptr; }
+};
+template <> struct PairLds<true> {
+  union {
+    SolveLds jacobi;
+    NewtonLds n;
+  };
+  __device__ NewtonLds& newton() { return n; }
+};
+
+// Pair problem k of submatrix p in the given round (PS_NT threads); whether it
+// rotated.  NEWTON: try newton_pair first (the FP64 path; the mixed path stops
+// its sweeps at a looser angle).
+template <bool NEWTON>
+__device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<NEWTON>& PL) {
+  SolveLds& L = PL.jacobi;
   const int npairs = e.nb / 2;
   int* flagR = flag_buf(e, round) + (int64_t)p * npairs + k;
   const int Mp = e.Mp;
@@ -255,9 +459,12 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, SolveLds
     dc[u] = B[(ct + u) * (int64_t)(Mp + 1)];
     dc[2 + u] = B[(cb + u) * (int64_t)(Mp + 1)];
   }
-  int need = 0;
+  int need = 0, far = 0;  // far: a rotation too large for Newton's iteration
   auto test = [&](double v, int row, int col, double a, double b) {
-    if (row < col && fabs(v) > fl && must_rotate(v, a, b, fl)) need = 1;
+    if (row < col && fabs(v) > fl) {
+      if (must_rotate(v, a, b, fl)) need = 1;
+      if (NEWTON && !(fabs(v) <= NEWTON_MAX * fabs(a - b))) far = 1;
+    }
   };
 #pragma unroll
   for (int m = 0; m < PS_R; ++m) {
@@ -269,6 +476,17 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, SolveLds
   if (!__syncthreads_or(need)) {
     if (threadIdx.x == 0) *flagR = 0;
     return false;
+  }
+  double* Rg = rot_buf(e, round) + ((int64_t)p * npairs + k) * B2 * B2;
+  if constexpr (NEWTON) {
+    if (!__syncthreads_or(far) && newton_pair(B, Mp, I, J, fl, Rg, PL.newton())) {
+      if (threadIdx.x == 0) {
+        *flagR = 1;
+        atomicAdd(&e.stats[2 * p + 1], 1);
+      }
+      return true;
+    }
+    __syncthreads();  // the sweeps reuse its LDS
   }
   const double* sc = scal_of(e, p);
   const double sigma = 2.0 * fmax(fabs(sc[1]), fabs(sc[2])) + TINY;
@@ -394,7 +612,6 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, SolveLds
   // eigenvectors: normalised columns of W, row-major: Rg[r * 2b + c] = R(r, c)
   exact_norms();
   const double iT0 = rsq_d(nT0), iT1 = rsq_d(nT1), iB0 = rsq_d(nB0), iB1 = rsq_d(nB1);
-  double* Rg = rot_buf(e, round) + ((int64_t)p * npairs + k) * B2 * B2;
 #pragma unroll
   for (int m = 0; m < PS_R; ++m) {
     *(double2*)&Rg[(row0 + m) * B2 + 2 * j] = make_double2(T0[m] * iT0, T1[m] * iT1);
@@ -407,15 +624,16 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, SolveLds
   return true;
 }
 
-__device__ inline void solve_block(const EighBatch& e, int sweep, int round, int b, SolveLds& L) {
+template <bool NEWTON>
+__device__ inline void solve_block(const EighBatch& e, int sweep, int round, int b, PairLds<NEWTON>& L) {
   const int npairs = e.nb / 2, p = b / npairs;
   if (!sweep_active(e, p, sweep)) return;
-  if (solve_pair(e, round, p, b % npairs, L) && threadIdx.x == 0) atomicMax(&e.state[2 * p], sweep + 1);
+  if (solve_pair<NEWTON>(e, round, p, b % npairs, L) && threadIdx.x == 0) atomicMax(&e.state[2 * p], sweep + 1);
 }
 
-__global__ __launch_bounds__(PS_NT) void pair_solve(EighBatch e, int sweep) {
-  __shared__ SolveLds L;
-  solve_block(e, sweep, 0, blockIdx.x, L);
+template <bool NEWTON> __global__ __launch_bounds__(PS_NT, 2) void pair_solve(EighBatch e, int sweep) {
+  __shared__ PairLds<NEWTON> L;
+  solve_block<NEWTON>(e, sweep, 0, blockIdx.x, L);
 }
 
 // 64x64x64 products with FP64 MFMA by NTH / 64 waves: wave w owns rows
@@ -611,16 +829,17 @@ __global__ __launch_bounds__(AB_NT) void pair_apply_b(EighBatch e, int sweep, in
 
 // The pair problems of round solve_round (the first P * npairs workgroups;
 // none when solve_round < 0) beside the U tiles of round u_round (the rest).
-__global__ __launch_bounds__(PS_NT) void pair_solve_apply_u(EighBatch e, int sweep, int solve_round, int u_round) {
+template <bool NEWTON>
+__global__ __launch_bounds__(PS_NT, NEWTON ? 2 : 3) void pair_solve_apply_u(EighBatch e, int sweep, int solve_round, int u_round) {
   __shared__ union {
-    SolveLds solve;
+    PairLds<NEWTON> solve;
     double T[B2][LS];
   } L;
   const int npairs = e.nb / 2;
   const int ns = solve_round >= 0 ? e.P * npairs : 0;
   const int b = blockIdx.x;
   if (b < ns) {
-    solve_block(e, sweep, solve_round, b, L.solve);
+    solve_block<NEWTON>(e, sweep, solve_round, b, L.solve);
   } else {
     const int per = (e.Mp / B2) * npairs, p = (b - ns) / per;
     if (sweep_active(e, p, sweep)) apply_u_tile<PS_NT>(e, u_round, p, (b - ns) % per, L.T);
@@ -632,9 +851,9 @@ __global__ __launch_bounds__(PS_NT) void pair_solve_apply_u(EighBatch e, int swe
 // is some ten times slower per sweep than the launches above, so it stands
 // behind enough of those (see eigh_run) that only start vectors
 // far from any the method is meant for reach it.
-__global__ __launch_bounds__(PS_NT) void sweeps_left(EighBatch e, int sweep, int max_sweeps) {
+template <bool NEWTON> __global__ __launch_bounds__(PS_NT, 2) void sweeps_left(EighBatch e, int sweep, int max_sweeps) {
   __shared__ union {
-    SolveLds solve;
+    PairLds<NEWTON> solve;
     double T[B2][LS];
   } L;
   const int p = blockIdx.x, npairs = e.nb / 2;
@@ -645,7 +864,7 @@ __global__ __launch_bounds__(PS_NT) void sweeps_left(EighBatch e, int sweep, int
     ran = sweep + 1;
     for (int round = 0; round < e.nb - 1; ++round) {
       for (int k = 0; k < npairs; ++k) {
-        if (solve_pair(e, round, p, k, L.solve)) rotated = sweep + 1;
+        if (solve_pair<NEWTON>(e, round, p, k, L.solve)) rotated = sweep + 1;
         __syncthreads();
       }
       for (int w = 0; w < npairs * (npairs + 1) / 2; ++w) {
@@ -721,7 +940,7 @@ __global__ void embed_x0(EighBatch e, T* __restrict__ X, int64_t ldx, double* __
 
 }  // namespace
 
-template <typename T>
+template <bool NEWTON, typename T>
 static hipError_t eigh_run(const EighBatch& e, const T* At, int64_t ldat, int max_sweeps, hipStream_t s) {
   const int npairs = e.nb / 2;
   const int nrc = e.Mp / B2;
@@ -740,26 +959,32 @@ static hipError_t eigh_run(const EighBatch& e, const T* At, int64_t ldat, int ma
     if (sw > 0) hipLaunchKernelGGL(sweep_scan, dim3(std::min(e.Mp, 64), e.P), dim3(256), 0, s, e, sw);
     // round r: B tiles, then the next round's pair problems beside the U tiles
     const int rounds = e.nb - 1;
-    hipLaunchKernelGGL(pair_solve, dim3(e.P * npairs), dim3(PS_NT), 0, s, e, sw);
+    hipLaunchKernelGGL(pair_solve<NEWTON>, dim3(e.P * npairs), dim3(PS_NT), 0, s, e, sw);
     for (int r = 0; r < rounds; ++r) {
       hipLaunchKernelGGL(pair_apply_b, dim3(e.P * (npairs * (npairs + 1) / 2)), dim3(AB_NT), 0, s, e, sw, r);
       const int next = r + 1 < rounds ? r + 1 : -1;
       const unsigned grid = (unsigned)((next >= 0 ? e.P * npairs : 0) + e.P * nrc * npairs);
-      hipLaunchKernelGGL(pair_solve_apply_u, dim3(grid), dim3(PS_NT), 0, s, e, sw, next, r);
+      hipLaunchKernelGGL(pair_solve_apply_u<NEWTON>, dim3(grid), dim3(PS_NT), 0, s, e, sw, next, r);
     }
   }
   if (spread < max_sweeps)
-    hipLaunchKernelGGL(sweeps_left, dim3(e.P), dim3(PS_NT), 0, s, e, spread, max_sweeps);
+    hipLaunchKernelGGL(sweeps_left<NEWTON>, dim3(e.P), dim3(PS_NT), 0, s, e, spread, max_sweeps);
   hipLaunchKernelGGL(rank_select, dim3(e.P, e.Mp / RS_NT), dim3(RS_NT), e.Mp * sizeof(double), s, e, max_sweeps);
   return hipGetLastError();
 }
 
+// The FP64 path is the one with the FP64 rotation floor.
+template <typename T>
+static hipError_t eigh_any(const EighBatch& e, const T* At, int64_t ldat, int max_sweeps, hipStream_t s) {
+  return e.floor_rel > 0.0 ? eigh_run<false>(e, At, ldat, max_sweeps, s) : eigh_run<true>(e, At, ldat, max_sweeps, s);
+}
+
 hipError_t eigh_batched_run(const EighBatch& e, const double* At, int64_t ldat, int max_sweeps, hipStream_t s) {
-  if (e.src_f32) return eigh_run(e, (const float*)At, ldat, max_sweeps, s);
-  return eigh_run(e, At, ldat, max_sweeps, s);
+  if (e.src_f32) return eigh_any(e, (const float*)At, ldat, max_sweeps, s);
+  return eigh_any(e, At, ldat, max_sweeps, s);
 }
 hipError_t eigh_batched_run(const EighBatch& e, const float* At, int64_t ldat, int max_sweeps, hipStream_t s) {
-  return eigh_run(e, At, ldat, max_sweeps, s);
+  return eigh_any(e, At, ldat, max_sweeps, s);
 }
 
 hipError_t embed_start_vectors(const EighBatch& e, float* X, int64_t ldx, double* eps, int64_t n, hipStream_t s) {
