@@ -237,15 +237,19 @@ struct SolveLds {
 // the sweeps' own test leaves it; otherwise, and when five steps do not do, the
 // result is false and the Jacobi sweeps take over.  About 12 us for one
 // product step against 33 us for each Jacobi sweep of the 64 x 64 problem.
+// A Jacobi sweep whose rotations were all below FINISH_ANGLE also hands over:
+// its normalised columns (given in L.X, start set) are off by about the square
+// of that.
 constexpr double NEWTON_MAX = 0.00390625;            // 2^-8
 constexpr double NEWTON_DONE = 9.313225746154785e-10;  // 2^-30
+constexpr double FINISH_ANGLE = 0.03125;             // 2^-5
 constexpr int NEWTON_STEPS = 5;
 struct NewtonLds {
   double X[B2][LS];
   double Y[B2][LS];
   double lam[B2];
 };
-__device__ bool newton_pair(const double* B, int Mp, int I, int J, double fl, double* Rg, NewtonLds& L) {
+__device__ bool newton_pair(const double* B, int Mp, int I, int J, double fl, double* Rg, NewtonLds& L, bool start) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l16 = lane & 15, lq = lane >> 4;
   const int i0 = (wave & 1) * 32, j0 = (wave >> 1) * 32;  // this wave's quadrant
@@ -259,8 +263,9 @@ __device__ bool newton_pair(const double* B, int Mp, int I, int J, double fl, do
 #pragma unroll
       for (int j = 0; j < 2; ++j) a[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
   };
-  if (threadIdx.x < B2) L.lam[threadIdx.x] = B[pair_idx(threadIdx.x, I, J) * (int64_t)(Mp + 1)];
-  for (int step = 0; step < NEWTON_STEPS; ++step) {
+  if (!start && threadIdx.x < B2) L.lam[threadIdx.x] = B[pair_idx(threadIdx.x, I, J) * (int64_t)(Mp + 1)];
+#pragma unroll 1
+  for (int step = start ? 1 : 0; step < NEWTON_STEPS; ++step) {
     if (step == 0) {
 #pragma unroll
       for (int ib = 0; ib < 2; ++ib)
@@ -274,23 +279,26 @@ __device__ bool newton_pair(const double* B, int Mp, int I, int J, double fl, do
           }
     } else {
       // Y = S X: S from memory (symmetric, its columns), X from LDS
-      double af[B2 / 4][2];
-#pragma unroll
-      for (int kk = 0; kk < B2 / 4; ++kk)
-#pragma unroll
-        for (int ib = 0; ib < 2; ++ib)
-          af[kk][ib] = B[pair_idx(row(ib), I, J) + (int64_t)pair_idx(4 * kk + lq, I, J) * Mp];
       clear(st);
+#pragma unroll 1
+      for (int kh = 0; kh < 2; ++kh) {  // eight k steps' fragments of S in flight
+        double af[B2 / 8][2];
 #pragma unroll
-      for (int kk = 0; kk < B2 / 4; ++kk) {
-        double bf[2];
+        for (int kk = 0; kk < B2 / 8; ++kk)
 #pragma unroll
-        for (int jb = 0; jb < 2; ++jb) bf[jb] = L.X[4 * kk + lq][j0 + 16 * jb + l16];
+          for (int ib = 0; ib < 2; ++ib)
+            af[kk][ib] = B[pair_idx(row(ib), I, J) + (int64_t)pair_idx(32 * kh + 4 * kk + lq, I, J) * Mp];
 #pragma unroll
-        for (int ib = 0; ib < 2; ++ib)
+        for (int kk = 0; kk < B2 / 8; ++kk) {
+          double bf[2];
 #pragma unroll
-          for (int jb = 0; jb < 2; ++jb)
-            st[ib][jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(bf[jb], af[kk][ib], st[ib][jb], 0, 0, 0);
+          for (int jb = 0; jb < 2; ++jb) bf[jb] = L.X[32 * kh + 4 * kk + lq][j0 + 16 * jb + l16];
+#pragma unroll
+          for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+            for (int jb = 0; jb < 2; ++jb)
+              st[ib][jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(bf[jb], af[kk][ib], st[ib][jb], 0, 0, 0);
+        }
       }
 #pragma unroll
       for (int ib = 0; ib < 2; ++ib)
@@ -302,7 +310,7 @@ __device__ bool newton_pair(const double* B, int Mp, int I, int J, double fl, do
       // X^T X and St = X^T Y
       clear(st);
       clear(xx);
-#pragma unroll
+#pragma unroll 2
       for (int kk = 0; kk < B2 / 4; ++kk) {
         double a2[2], bx[2], by[2];
 #pragma unroll
@@ -379,7 +387,7 @@ __device__ bool newton_pair(const double* B, int Mp, int I, int J, double fl, do
           for (int r = 0; r < 4; ++r) L.Y[row(ib)][col(jb, r)] = st[ib][jb][r];
       __syncthreads();
       clear(st);
-#pragma unroll
+#pragma unroll 4
       for (int kk = 0; kk < B2 / 4; ++kk) {
         double a2[2], b2[2];
 #pragma unroll
@@ -478,16 +486,6 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<
     return false;
   }
   double* Rg = rot_buf(e, round) + ((int64_t)p * npairs + k) * B2 * B2;
-  if constexpr (NEWTON) {
-    if (!__syncthreads_or(far) && newton_pair(B, Mp, I, J, fl, Rg, PL.newton())) {
-      if (threadIdx.x == 0) {
-        *flagR = 1;
-        atomicAdd(&e.stats[2 * p + 1], 1);
-      }
-      return true;
-    }
-    __syncthreads();  // the sweeps reuse its LDS
-  }
   const double* sc = scal_of(e, p);
   const double sigma = 2.0 * fmax(fabs(sc[1]), fabs(sc[2])) + TINY;
   auto shift = [&](double v, int row, int col, int gcol) {
@@ -537,8 +535,22 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<
   const double angle = e.angle > 0.0 ? e.angle : ANGLE;
   bool converged = false;
   int par = 0;
+  bool newton = NEWTON && !__syncthreads_or(far), start = false;
   for (int sweep = 0; sweep < e.inner_max_sweeps; ++sweep) {
-    unsigned long long big = 0;  // lanes that rotated by more than the stopping angle
+    if constexpr (NEWTON) {
+      if (newton) {
+        if (newton_pair(B, Mp, I, J, fl, Rg, PL.newton(), start)) {
+          if (threadIdx.x == 0) {
+            *flagR = 1;
+            atomicAdd(&e.stats[2 * p + 1], 1);
+          }
+          return true;
+        }
+        newton = false;
+        __syncthreads();  // the sweeps reuse its LDS
+      }
+    }
+    unsigned long long big = 0, wide = 0;  // lanes that rotated by more than the stopping / finishing angle
     exact_norms();
 #pragma unroll 1
     for (int r = 0; r < B2 - 1; ++r) {
@@ -579,6 +591,7 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<
       s0 = rot ? s0 : 0.0;
       // only rotations by more than the stopping angle keep the sweep going (see above)
       big |= __ballot(fabs(s0) > angle);
+      if constexpr (NEWTON) wide |= __ballot(fabs(s0) > FINISH_ANGLE);
       // the squared norms change by -+ tan t ab, 1 / cos t = ic
       double x0 = rot ? s0 * ic * ab : 0.0, c1 = c0, s1 = s0, x1 = x0;
       swap32_d(c0, c1);
@@ -602,6 +615,22 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<
     if (!big) {
       converged = true;
       break;
+    }
+    if constexpr (NEWTON) {
+      if (!wide) {
+        exact_norms();
+        const double iT0 = rsq_d(nT0), iT1 = rsq_d(nT1), iB0 = rsq_d(nB0), iB1 = rsq_d(nB1);
+        __syncthreads();  // the norms have been read; X takes their place
+        double (*X)[LS] = PL.newton().X;
+#pragma unroll
+        for (int m = 0; m < PS_R; ++m) {
+          X[row0 + m][2 * j] = T0[m] * iT0;
+          X[row0 + m][2 * j + 1] = T1[m] * iT1;
+          X[row0 + m][62 - 2 * j] = B1[m] * iB1;
+          X[row0 + m][63 - 2 * j] = B0[m] * iB0;
+        }
+        newton = start = true;
+      }
     }
   }
   // The normalised columns are orthonormal eigenvectors only once every
