@@ -29,7 +29,8 @@ constexpr int TILE_BYTES = BM * ROWB;     // 36864 per operand per stage
 //   CFG 4: 8 waves in 4 x 2 fed by direct global -> LDS loads into a 4-stage
 //          ring (gemm_x3_dl)
 //   CFG 5: CFG 4 with the LDS fragments of the next stage read while the
-//          MFMAs of the current one run
+//          MFMAs of the current one run, in tiles of 128 or 64 (gemm_x3_t) where
+//          those of 256 leave CUs idle
 template <int CFG> struct X3Cfg;
 template <> struct X3Cfg<0> { static constexpr int NT = 512, WGR = 2, WR = 4, WC = 2, PF = 0; };
 template <> struct X3Cfg<1> { static constexpr int NT = 256, WGR = 2, WR = 4, WC = 4, PF = 0; };
@@ -84,10 +85,10 @@ __device__ inline void x3_tile_coords(const X3Args& g, int tiles_m, int tiles_n,
 
 // k range of a tile (multiples of 32): the optional per-column-tile and
 // per-row-tile ranges, clipped in the KPREFIX mode (op(B) upper triangular).
-__device__ inline void x3_k_range(const X3Args& g, int tm, int tn, int64_t m0, int64_t n0, int64_t& kbeg,
-                                   int64_t& kend) {
+__device__ inline void x3_k_range(const X3Args& g, int64_t m0, int64_t n0, int64_t& kbeg, int64_t& kend) {
   kbeg = 0;
   kend = (g.K + 31) / 32 * 32;
+  const int64_t tm = m0 / BM, tn = n0 / BN;  // the tables go by tiles of 256, whatever the tile
   if (g.krange) {
     kbeg = g.krange[2 * tn];
     kend = g.krange[2 * tn + 1];
@@ -96,7 +97,7 @@ __device__ inline void x3_k_range(const X3Args& g, int tm, int tn, int64_t m0, i
     kbeg = max<int64_t>(kbeg, g.krange_rows[2 * tm]);
     kend = min<int64_t>(kend, g.krange_rows[2 * tm + 1]);
   }
-  if (g.tiles == X3_KPREFIX) kend = min<int64_t>(kend, n0 + BN);
+  if (g.tiles == X3_KPREFIX) kend = min<int64_t>(kend, (tn + 1) * BN);
 }
 
 // Gate of the band / full forms of a folded-spectrum product (see X3Args):
@@ -120,7 +121,7 @@ __device__ inline float bf2f(bf16_t h) { return __builtin_bit_cast(float, (uint3
 
 // Epilogue shared by the split-BF16 kernels: acc[ib][jb][r] is C(i, j) with
 // i = wi0 + 32 ib + lane % 32, j = wj0 + 32 jb + 8 (r / 4) + 4 (lane / 32) + r % 4.
-template <int EPI, int WGR, int WR, int WC>
+template <int EPI, int WGR, int WR, int WC, int BN = X3_BN>
 __device__ inline void x3_epilogue(const X3Args& g, v16f (&acc)[WR][WC], int64_t m0, int64_t n0, int wi0, int wj0,
                                    int tid, int tm, double (*red)[BN]) {
   const int lane = tid & 63, wave = tid >> 6;
@@ -164,7 +165,7 @@ __device__ inline void x3_epilogue(const X3Args& g, v16f (&acc)[WR][WC], int64_t
   // rows outside [fk0, fk1) are the far rows of this column tile
   int64_t fk0 = 0, fk1 = 0;
   if ((EPI == X3_SHIFT || EPI == X3_FSUPD) && g.farmax_out) {
-    const int64_t tn = n0 / BN;
+    const int64_t tn = n0 / X3_BN;
     fk0 = g.far_krange[2 * tn];
     fk1 = g.far_krange[2 * tn + 1];
   }
@@ -268,7 +269,7 @@ __global__ __launch_bounds__(X3Cfg<CFG>::NT, 1) void gemm_x3_kernel(X3Args g, in
   const int wi0 = (wave % WGR) * (32 * WR), wj0 = (wave / WGR) * (32 * WC);
   const int l32 = lane & 31, lh = lane >> 5;
   int64_t kbeg, kend;
-  x3_k_range(g, tm, tn, m0, n0, kbeg, kend);
+  x3_k_range(g, m0, n0, kbeg, kend);
 
   v16f acc[WR][WC];
 #pragma unroll
@@ -412,7 +413,7 @@ __global__ __launch_bounds__(512, 1) void gemm_x3_dl(X3Args g, int tiles_m, int 
   const int wi0 = (wave % WGR) * (32 * WR), wj0 = (wave / WGR) * (32 * WC);
   const int l32 = lane & 31, lh = lane >> 5;
   int64_t kbeg, kend;
-  x3_k_range(g, tm, tn, m0, n0, kbeg, kend);
+  x3_k_range(g, m0, n0, kbeg, kend);
   if (unit >= 0) {  // piece unit % S of S equal runs of k16 stages
     const int64_t st = kend > kbeg ? (kend - kbeg) / 16 : 0, sl = unit % g.split_s;
     const int64_t b0 = kbeg + 16 * (st * sl / g.split_s), b1 = kbeg + 16 * (st * (sl + 1) / g.split_s);
@@ -583,6 +584,147 @@ __global__ __launch_bounds__(512, 1) void gemm_x3_dl(X3Args g, int tiles_m, int 
     return;
   }
   x3_epilogue<EPI, WGR, WR, WC>(g, acc, m0, n0, wi0, wj0, tid, tm, red);
+}
+
+// Configuration 5 for products whose tiles of 256 would not fill the chip: 4
+// waves in 2 x 2, a wave tile of WR x WC MFMA blocks (block tiles of 128 or
+// 64), the ring and stages of gemm_x3_dl filled by buffer loads.  The
+// fragments of stage t + 1 are read from LDS and the loads of stage t + 3
+// issued between the MFMAs of stage t; stages past the last read rows' ends
+// or, past the operand, zeros, and are never multiplied, so the loop has no
+// branch but its own.  Each accumulator takes its products in the same order
+// whatever the tile, so all tile sizes agree bit for bit.
+typedef unsigned char uchar;
+__device__ inline void load_lds16(__amdgpu_buffer_rsrc_t r, uchar* dst, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (void __attribute__((address_space(3)))*)dst, 16, off, 0, 0, 0);
+}
+
+template <int EPI, int NP, int WR, int WC>
+__global__ __launch_bounds__(256, 2) void gemm_x3_t(X3Args g, int tiles_m, int tiles_n) {
+  constexpr int TM = 64 * WR, TN = 64 * WC, LA = TM / 64, LB = TN / 64;  // loads per wave and stage
+  constexpr int STAGE = (TM + TN) * DROW;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  if (x3_gate_closed(g)) return;
+  if (g.band_count && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(g.band_count, 1u);
+  int tm, tn;
+  x3_tile_coords(g, tiles_m, tiles_n, tm, tn);
+  const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wi0 = (wave & 1) * 32 * WR, wj0 = (wave >> 1) * 32 * WC;
+  const int l32 = lane & 31, lh = lane >> 5;
+  int64_t kbeg, kend;
+  x3_k_range(g, m0, n0, kbeg, kend);
+  constexpr int SK = NP == 1 ? 32 : 16;  // k values per stage
+  const int total = kend > kbeg ? (int)((kend - kbeg) / SK) : 0;
+
+  // byte offsets of this lane's 16-byte chunk in each 16-row group it loads
+  uint32_t offA[LA], offB[LB];
+#pragma unroll
+  for (int j = 0; j < LA; ++j) {
+    const int row = 16 * (wave * LA + j) + (lane >> 2), c = (lane & 3) ^ dswz(row);
+    const int64_t r = m0 + row < g.M ? row : g.M - 1 - m0;  // rows past the edge: the last one
+    offA[j] = (uint32_t)(r * g.ldap * 2 + (NP == 1 ? 16 * c : (c >> 1) * 64 + (c & 1) * 16));
+  }
+#pragma unroll
+  for (int j = 0; j < LB; ++j) {
+    const int row = 16 * (wave * LB + j) + (lane >> 2), c = (lane & 3) ^ dswz(row);
+    const int64_t r = n0 + row < g.N ? row : g.N - 1 - n0;
+    offB[j] = (uint32_t)(r * g.ldbp * 2 + (NP == 1 ? 16 * c : (c >> 1) * 64 + (c & 1) * 16));
+  }
+  const uchar* baseA = (const uchar*)(g.Ap + m0 * g.ldap);
+  const uchar* baseB = (const uchar*)(g.Bp + n0 * g.ldbp);
+  const int64_t sizeA = (g.M - m0) * g.ldap * 2, sizeB = (g.N - n0) * g.ldbp * 2;  // bytes from the base to the end
+  auto in_range = [](int64_t rest) { return rest <= 0 ? 0 : rest > 0x7fffffff ? 0x7fffffff : (int)rest; };
+  auto issue = [&](int t) {
+    const int64_t k0 = kbeg + SK * (int64_t)t;
+    const int64_t koff = NP == 1 ? 2 * k0 : (k0 >> 5) * 128 + ((k0 >> 4) & 1) * 32;
+    const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)(baseA + koff), 0, in_range(sizeA - koff), 0x00027000);
+    const auto rb = __builtin_amdgcn_make_buffer_rsrc((void*)(baseB + koff), 0, in_range(sizeB - koff), 0x00027000);
+    uchar* sA = lds + (t % DST) * STAGE;
+    uchar* sB = sA + TM * DROW;
+#pragma unroll
+    for (int j = 0; j < LA; ++j)
+      load_lds16(ra, sA + (wave * LA + j) * 1024, offA[j]);
+#pragma unroll
+    for (int j = 0; j < LB; ++j)
+      load_lds16(rb, sB + (wave * LB + j) * 1024, offB[j]);
+  };
+
+  v16f acc[WR][WC];
+#pragma unroll
+  for (int i = 0; i < WR; ++i)
+#pragma unroll
+    for (int j = 0; j < WC; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  struct Frags {
+    v8bf ah[WR], al[WR], bh[WC], bl[WC];
+  };
+  auto read_frags = [&](int t, Frags& f) {
+    const uchar* Ab = lds + (t % DST) * STAGE;
+    const uchar* Bb = Ab + TM * DROW;
+#pragma unroll
+    for (int ib = 0; ib < WR; ++ib) {
+      const int row = wi0 + ib * 32 + l32, sw = dswz(row);
+      f.ah[ib] = as_bf(*(const u32x4*)(Ab + row * DROW + 16 * (lh ^ sw)));
+      f.al[ib] = as_bf(*(const u32x4*)(Ab + row * DROW + 16 * ((2 + lh) ^ sw)));
+    }
+#pragma unroll
+    for (int jb = 0; jb < WC; ++jb) {
+      const int row = wj0 + jb * 32 + l32, sw = dswz(row);
+      f.bh[jb] = as_bf(*(const u32x4*)(Bb + row * DROW + 16 * (lh ^ sw)));
+      f.bl[jb] = as_bf(*(const u32x4*)(Bb + row * DROW + 16 * ((2 + lh) ^ sw)));
+    }
+  };
+  auto mma = [&](const Frags& f) {
+    // product-major order: consecutive MFMAs update different accumulators
+#pragma unroll
+    for (int pr = 0; pr < (NP == 3 ? 3 : 2); ++pr)
+#pragma unroll
+      for (int ib = 0; ib < WR; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < WC; ++jb)
+          acc[ib][jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pr == 1 ? f.bl[jb] : f.bh[jb],
+                                                                (NP == 3 ? pr == 2 : pr == 1) ? f.al[ib] : f.ah[ib],
+                                                                acc[ib][jb], 0, 0, 0);
+  };
+  constexpr int LW = LA + LB, NR = 2 * (WR + WC), NM = (NP == 3 ? 3 : 2) * WR * WC;
+  if (total > 0) {
+    issue(0);
+    issue(1);
+    issue(2);
+    wait_vm<2 * LW>();
+    lds_barrier();
+    Frags F0, F1;
+    read_frags(0, F0);
+    auto step = [&](int t, Frags& cur, Frags& nxt) {
+      wait_vm<LW>();  // this wave's part of stage t + 1 has landed (stage t + 2 may be in flight)
+      lds_barrier();  // everyone's has, and stage t - 1 is consumed
+      __builtin_amdgcn_sched_barrier(0);
+      issue(t + 3);
+      read_frags(t + 1, nxt);
+      mma(cur);
+#pragma unroll
+      for (int u = 0; u < NR; ++u) {
+        __builtin_amdgcn_sched_group_barrier(0x008, NM / NR, 0);  // MFMA
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);        // LDS read
+        if (u % 2 == 0) __builtin_amdgcn_sched_group_barrier(0x020, (2 * LW + NR - 1) / NR, 0);  // global -> LDS loads
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    int t = 0;
+#pragma unroll 1
+    for (; t + 1 < total; t += 2) {
+      step(t, F0, F1);
+      step(t + 1, F1, F0);
+    }
+    if (t < total) step(t, F0, F1);
+  }
+  wait_vm<0>();
+  __syncthreads();  // no load may still be landing, no wave reading, when shared memory is reused
+  x3_epilogue<EPI, 2, WR, WC, TN>(g, acc, m0, n0, wi0, wj0, tid, tm, (double (*)[TN])lds);
 }
 
 // Sum of the S K pieces of each split tail tile (fixed order) and the STORE
@@ -917,6 +1059,44 @@ hipError_t x3_init() {
   return e;
 }
 
+namespace {
+// Block tile (256, 128 or 64) of a configuration-5 product: the least of the
+// measured times per 32 values of k (us, one round of tiles over the chip's
+// CUs, plus what a round costs whatever its number): three products 2.1 r for
+// tiles of 256, 0.2 + 0.67 r for 128, 0.3 + 0.28 r for 64 (r: tiles per CU,
+// rounded up); one product 1.05 r, 0.3 + 0.32 r, 0.27 + 0.13 r.  N = 607:
+// 57.8 / 24.0 / 12.9 us by tile; 1024: 79 / 32 / 19; 2048: 135 / 58 / 81; 4096:
+// 317 / 360 / 578.
+int x3_tile(const X3Args& a) {
+  const bool one = a.products == 1;
+  auto rounds = [&](int64_t b) {
+    const int64_t m = (a.M + b - 1) / b, n = (a.N + b - 1) / b;
+    return (double)(((a.tiles == X3_LOWER ? m * (m + 1) / 2 : m * n) + x3_num_cu - 1) / x3_num_cu);
+  };
+  const double t256 = (one ? 1.05 : 2.1) * rounds(256);
+  const double t128 = one ? 0.3 + 0.32 * rounds(128) : 0.2 + 0.67 * rounds(128);
+  const double t64 = one ? 0.27 + 0.13 * rounds(64) : 0.3 + 0.28 * rounds(64);
+  if (t64 <= t128 && t64 < t256) return 64;
+  return t128 < t256 ? 128 : 256;
+}
+
+template <int E, int WR>
+hipError_t launch_t(const X3Args& a, hipStream_t s) {
+  constexpr int T = 64 * WR;
+  const int tm = (int)((a.M + T - 1) / T), tn = (int)((a.N + T - 1) / T);
+  const dim3 grid(a.tiles == X3_LOWER ? tm * (tm + 1) / 2 : tm * tn);
+  constexpr size_t lds = DST * 2 * T * DROW;
+  if constexpr (E == X3_SHIFT || E == X3_FSUPD || E == X3_ADD) {
+    if (a.products == 1) {
+      hipLaunchKernelGGL((gemm_x3_t<E, 1, WR, WR>), grid, dim3(256), lds, s, a, tm, tn);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((gemm_x3_t<E, 3, WR, WR>), grid, dim3(256), lds, s, a, tm, tn);
+  return hipGetLastError();
+}
+}  // namespace
+
 template <int E>
 void launch_dl(bool one, bool pipe, int total, size_t dl, hipStream_t s, const X3Args& b, int tm, int tn) {
   if constexpr (E == X3_SHIFT || E == X3_FSUPD || E == X3_ADD) {
@@ -967,6 +1147,23 @@ hipError_t gemm_x3(int epi, const X3Args& a, hipStream_t s) {
             b.split_s = S;
             total = b.split_full + rem * S;
           }
+        }
+      }
+      // lower-tile products of more than one wave keep their tiles of 256: their
+      // tail is the one split along K, and its sums with it
+      const bool small = cfg == 5 && epi != X3_RQ && x3_num_cu > 0 && !(a.tiles == X3_LOWER && total > x3_num_cu);
+      const int tile = small ? x3_tile(b) : 256;
+      if (tile < 256) {
+        switch (epi) {
+#define X3_T_CASE(E) \
+  case E: return tile == 128 ? launch_t<E, 2>(b, s) : launch_t<E, 1>(b, s);
+          X3_T_CASE(X3_STORE)
+          X3_T_CASE(X3_SHIFT)
+          X3_T_CASE(X3_FSUPD)
+          X3_T_CASE(X3_ADD)
+          X3_T_CASE(X3_STORE_PACK)
+#undef X3_T_CASE
+          default: return hipErrorInvalidValue;
         }
       }
       switch (epi) {

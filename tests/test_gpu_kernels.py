@@ -258,6 +258,29 @@ def _pack_plain(x, dev):
     return P, ldq
 
 
+@pytest.mark.parametrize("tiles", [0, 1, 3])  # full, lower, K prefix
+@pytest.mark.parametrize("n,K", [(1, 1), (65, 33), (300, 64), (607, 607), (1100, 96), (2050, 160), (3001, 40)])
+def test_gemm_x3_tiles_agree(dev, tiles, n, K):
+    """Configuration 5 in its block tiles of 64, 128 and 256 (by order) gives
+    the bits of configuration 4's tiles of 256: every accumulator takes the
+    same products in the same order."""
+    if tiles == 3 and K < n:
+        K = n  # the prefix mode's right operand is square
+    g = torch.Generator(device=dev).manual_seed(n)
+    L = lib()
+    ldp = L.pfsm_test_x3_row_stride(K)
+    A, B = ((torch.randn(n, ldp, generator=g, device=dev)).to(torch.bfloat16) for _ in range(2))
+    outs = []
+    for cfg in (4, 5):
+        C = torch.zeros((n, n), dtype=torch.float32, device=dev)
+        assert L.pfsm_test_gemm_x3(0, cfg, tiles, n, n, K, _p(A), ldp, _p(B), ldp, _p(C), n, 0, 1.0, 0.0, None, 0, None, 0,
+                                   0, None, None, _stream()) == 0
+        outs.append(C.t())
+    i = torch.arange(n, device=dev)
+    keep = (i[:, None] >= i[None, :]) if tiles == 1 else torch.ones(n, n, dtype=torch.bool, device=dev)
+    assert torch.equal(outs[0][keep], outs[1][keep])
+
+
 def test_pack_plain_layout(dev):
     g = np.random.default_rng(5)
     K, R = 100, 37
