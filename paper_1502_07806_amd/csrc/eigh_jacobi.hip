@@ -980,10 +980,11 @@ static hipError_t eigh_run(const EighBatch& e, const T* At, int64_t ldat, int ma
   // Sweeps with one launch per round and kind of tile; launches of the sweeps
   // that a submatrix does not need cost about 2.4 us each (31 per sweep at
   // order 512), so only a margin over the usual count is enqueued this way: a
-  // basis close to the eigenvectors takes one active sweep to the mixed path's
-  // floor and two to the FP64 one, a single submatrix (a full diagonalisation
-  // from any basis) about ten.
-  const int spread = std::min(max_sweeps, e.P == 1 ? 16 : e.floor_rel > 0.0 ? 4 : 6);
+  // basis close to the eigenvectors (V = Q exp(K), ||K||_F = 0.01) takes one
+  // active sweep to the mixed path's floor and two to the FP64 one, one that
+  // mixes every level (||K||_F = 3) three and four; a single submatrix (a full
+  // diagonalisation from any basis) about ten.
+  const int spread = std::min(max_sweeps, e.P == 1 ? 16 : e.floor_rel > 0.0 ? 3 : 4);
   for (int sw = 0; sw < spread; ++sw) {
     if (sw > 0) hipLaunchKernelGGL(sweep_scan, dim3(std::min(e.Mp, 64), e.P), dim3(256), 0, s, e, sw);
     // round r: B tiles, then the next round's pair problems beside the U tiles
