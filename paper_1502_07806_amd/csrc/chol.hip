@@ -2,9 +2,8 @@
 // triangular solve X <- X L^{-T} (the orthonormalisation step, computed as
 // Cholesky-QR).
 //
-// Two-level blocking: 64-wide diagonal blocks are factored by one wavefront
-// with each lane holding one row in registers (column values are broadcast
-// through LDS), which also forms L_kk^{-T}; the 64-wide panel solve is an
+// Two-level blocking: 64-wide diagonal blocks are factored by one workgroup
+// (potrf_diag), which also forms L_kk^{-T}; the 64-wide panel solve is an
 // MFMA GEMM with that inverse; updates inside a 512-wide panel are rank-64
 // GEMMs restricted to the panel, and the rest of the matrix receives one
 // rank-512 update per panel, so the trailing matrix is streamed N/512 times
@@ -27,7 +26,7 @@ __device__ inline double readlane_d(double v, int l) {
 
 // Factor S[k0:k0+nb, k0:k0+nb] (lower triangle) in place and write
 // T = L^{-T} (upper triangular, 64 x 64 column-major; identity padding past
-// nb).  512 threads in two groups of four waves.  Factor group: thread
+// nb), for the one-launch-per-block fallback.  512 threads in two groups of four waves.  Factor group: thread
 // (w, i) holds row i of L, columns 16w .. 16w+15, in registers.  Step j:
 // the wave owning column j takes the pivot from lane j (readlane), scales
 // the column by one reciprocal square root (as LAPACK's unblocked Cholesky
@@ -144,8 +143,135 @@ __device__ inline void potrf_block(double* S, int64_t lds, int64_t k0, int nb, d
   }
 }
 
-__global__ __launch_bounds__(512) void potrf_diag(double* S, int64_t lds, int64_t k0, int nb, double* T, int* info) {
-  potrf_block(S, lds, k0, nb, T, info);
+// The same for the blocked factorisation, in panels of 16 columns (256
+// threads).  Wave 0 factors a panel: lane (q, i) holds row i of the diagonal
+// block (the same in every 16-lane row) and row i of another block - the q-th
+// below the diagonal one, or, for q = 3, of the identity, which becomes
+// L_kk^{-T} - so that every multiplier is a broadcast inside the 16-lane row
+// (a DPP operand; readlane through the scalar registers cost 60 cycles a column).
+// Then all waves update the columns past the panel with matrix-core products,
+// and during the next panel waves 1..3 form the finished block row of the
+// inverse, N(k, j) = -N(k, k) sum over j <= t < k of L(k, t) N(t, j).
+// What bounds it is the chain of 64 pivots, 0.13 us each: 14.6 us a launch
+// against 34 us with a barrier per column (of both, 2.5 us load and store).
+constexpr int PB = 16, NPB = NB / PB;
+__device__ inline double rsq_newton(double d) {  // third-order step on the hardware estimate (error below one ulp)
+  const double r = __builtin_amdgcn_rsq(d), e = fma(-(d * r), r, 1.0);
+  return fma(r * e, fma(0.375, e, 0.5), r);
+}
+template <int I>
+__device__ inline double row_bcast(double v) {  // lane I of each 16-lane row
+  const long long b = __double_as_longlong(v);
+  return __longlong_as_double(__builtin_amdgcn_update_dpp(b, b, 0x150 + I, 0xf, 0xf, true));
+}
+template <int J, int T>
+__device__ inline void panel_update(double (&r)[PB], double (&p)[PB], double l, double lp) {
+  if constexpr (T < PB) {
+    const double m = row_bcast<T>(l);
+    r[T] = fma(-l, m, r[T]);
+    p[T] = fma(-lp, m, p[T]);
+    panel_update<J, T + 1>(r, p, l, lp);
+  }
+}
+// Columns J.. of a panel; bad: its first pivot that is not positive (PB: none).
+template <int J>
+__device__ inline void panel_factor(double (&r)[PB], double (&p)[PB], int& bad) {
+  if constexpr (J < PB) {
+    const double d = row_bcast<J>(r[J]);
+    if (!(d > 0.0)) bad = min(bad, J);
+    const double inv = rsq_newton(d);  // NaN for such a d
+    r[J] *= inv;
+    p[J] *= inv;
+    panel_update<J, J + 1>(r, p, r[J], p[J]);
+    panel_factor<J + 1>(r, p, bad);
+  }
+}
+__global__ __launch_bounds__(256) void potrf_diag(double* S, int64_t lds, int64_t k0, int nb, double* T, int* info) {
+  __shared__ double L[NB][NB + 1], N[NB][NB + 1], W[NPB - 1][PB][PB + 1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lq = lane >> 4;
+  double* Sk = S + k0 + k0 * lds;
+  double v[NB * NB / 256];
+#pragma unroll
+  for (int m = 0; m < NB * NB / 256; ++m) v[m] = Sk[min(lane, nb - 1) + min(wave + 4 * m, nb - 1) * lds];
+#pragma unroll
+  for (int m = 0; m < NB * NB / 256; ++m) {
+    const int i = lane, c = wave + 4 * m;
+    L[i][c] = i < nb && c < nb && c <= i ? v[m] : i == c ? 1.0 : 0.0;
+    N[i][c] = 0.0;
+  }
+  __syncthreads();
+  // block row k of the inverse, one block per wave (j = wave - 1)
+  auto inverse_row = [&](int k) {
+    const int j = wave - 1;
+    if (j < 0 || j >= k) return;
+    v4d acc = {0.0, 0.0, 0.0, 0.0};
+    for (int t = j; t < k; ++t)
+#pragma unroll
+      for (int kk = 0; kk < PB; kk += 4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(N[PB * t + kk + lq][PB * j + l16], L[PB * k + l16][PB * t + kk + lq],
+                                                   acc, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) W[j][l16][lq + 4 * r] = acc[r];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int kk = 0; kk < PB; kk += 4)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(W[j][kk + lq][l16], N[PB * k + l16][PB * k + kk + lq], acc, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) N[PB * k + l16][PB * j + lq + 4 * r] = -acc[r];
+  };
+#pragma unroll 1
+  for (int kb = 0; kb < NPB; ++kb) {
+    const int c0 = PB * kb;
+    if (wave == 0) {
+      const int rb = lq == 3 ? NPB : kb + 1 + lq;  // block of the lane's second row; NPB: identity, past it: none
+      const bool mat = lq < 3 && rb < NPB;
+      const int prow = mat ? PB * rb + l16 : 0;
+      double r[PB], p[PB];
+#pragma unroll
+      for (int j = 0; j < PB; ++j) r[j] = L[c0 + l16][c0 + j], p[j] = L[prow][c0 + j];
+#pragma unroll
+      for (int j = 0; j < PB; ++j) p[j] = mat ? p[j] : (lq == 3 && j == l16) ? 1.0 : 0.0;
+      int bad = PB;
+      panel_factor<0>(r, p, bad);
+      if (lane == 0 && c0 + bad < min(nb, c0 + PB)) atomicCAS(info, 0, (int)(k0 + c0 + bad + 1));
+      double* dst = mat ? &L[prow][c0] : lq == 3 ? &N[c0][c0 + l16] : nullptr;
+      const int step = mat ? 1 : NB + 1;
+      if (dst)
+#pragma unroll
+        for (int j = 0; j < PB; ++j) dst[j * step] = p[j];
+      if (lq == 0)
+#pragma unroll
+        for (int j = 0; j < PB; ++j)
+          if (j <= l16) L[c0 + l16][c0 + j] = r[j];
+    } else if (kb > 1) {
+      inverse_row(kb - 1);
+    }
+    __syncthreads();
+    // columns past the panel: blocks (ib, jb), kb < jb <= ib, dealt to the waves
+    int b = 0;
+    for (int ib = kb + 1; ib < NPB; ++ib)
+      for (int jb = kb + 1; jb <= ib; ++jb, ++b) {
+        if ((b & 3) != wave) continue;
+        v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int kk = 0; kk < PB; kk += 4)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(L[PB * jb + l16][c0 + kk + lq], L[PB * ib + l16][c0 + kk + lq], acc,
+                                                     0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) L[PB * ib + l16][PB * jb + lq + 4 * r] -= acc[r];
+      }
+    __syncthreads();
+  }
+  inverse_row(NPB - 1);
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < NB * NB / 256; ++m) {
+    const int i = lane, c = wave + 4 * m;
+    if (i < nb && c < nb && c <= i) Sk[i + c * lds] = L[i][c];
+    T[i + c * NB] = N[c][i];  // T = L^{-T}; identity past nb
+  }
 }
 
 // ------------------------------------------------------------------------
@@ -329,7 +455,7 @@ hipError_t cholesky_factor(double* S, int64_t lds, int64_t n, double* Tbuf, int*
     for (int64_t k0 = K0; k0 < K0 + w; k0 += NB) {
       const int nb = (int)std::min<int64_t>(NB, K0 + w - k0);
       double* T = Tbuf + (k0 / NB) * NB * NB;
-      hipLaunchKernelGGL(potrf_diag, dim3(1), dim3(512), 0, s, S, lds, k0, nb, T, info);
+      hipLaunchKernelGGL(potrf_diag, dim3(1), dim3(256), 0, s, S, lds, k0, nb, T, info);
       const int64_t rest = n - k0 - nb;
       double* L21 = S + (k0 + nb) + k0 * lds;
       // panel: L21 = S21 T (in place; one column tile per row tile)

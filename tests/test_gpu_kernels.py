@@ -491,6 +491,34 @@ def test_cholesky_qr_gated_breakdown(dev, n, k):
     assert int(info.item()) == cholesky_lower(S0)[1] == k + 1
 
 
+@pytest.mark.parametrize("n", [1, 15, 17, 33, 63, 65])
+def test_cholesky_diag_block_edges(dev, n):
+    """Panels of 16 inside a 64-wide diagonal block, cut at any column: the factor,
+    and the block inverse T = L^{-T}, whose residual L T^T - I is of the order of
+    n unit roundoffs times |L| |T^T| (bound: 64 of these, as for the factor)."""
+    from oracle.pfsm_ref import cholesky_lower
+    S0 = _spd(n, n)
+    S = _cm(S0, dev)
+    nblk = (n + 63) // 64
+    T = torch.full((nblk * 4096,), np.nan, dtype=torch.float64, device=dev)
+    info = torch.zeros(1, dtype=torch.int32, device=dev)
+    assert lib().pfsm_test_cholesky(_p(S), n, n, _p(T), _p(info), _stream()) == 0
+    torch.cuda.synchronize()
+    L_ref, info_ref = cholesky_lower(S0)
+    assert int(info.item()) == info_ref == 0
+    L = np.tril(_np(S))
+    assert np.max(np.abs(L - L_ref)) <= 64 * n * U64 * np.abs(L_ref).max()
+    assert np.array_equal(np.triu(_np(S), 1), np.triu(S0, 1))  # the upper triangle is not touched
+    for b in range(nblk):
+        Lb = np.eye(64)
+        w = min(64, n - 64 * b)
+        Lb[:w, :w] = L[64 * b:64 * b + w, 64 * b:64 * b + w]
+        Tt = T[4096 * b:4096 * (b + 1)].cpu().numpy().reshape(64, 64)  # column-major T, read as T^T
+        assert np.array_equal(np.triu(Tt, 1), np.zeros((64, 64)))
+        bound = 64 * 64 * U64 * np.max(np.abs(Lb) @ np.abs(Tt))
+        assert np.max(np.abs(Lb @ Tt - np.eye(64))) <= bound
+
+
 @pytest.mark.parametrize("n,k", [(200, 0), (200, 130), (1100, 777)])
 def test_cholesky_breakdown_column(dev, n, k):
     """A non-positive pivot at global column k reports info = k + 1 (first one wins)."""
