@@ -83,6 +83,10 @@ __device__ inline void pair_blocks(int k, int r, int nb, int& I, int& J) {
 // global index (within the padded submatrix) of local index t in [0, 2b) of pair (I, J)
 __device__ inline int pair_idx(int t, int I, int J) { return t < EIGH_B ? I * EIGH_B + t : J * EIGH_B + (t - EIGH_B); }
 
+// Counters of sweeps_left {tickets taken, tasks done}, in the ranking's memory,
+// which nothing uses before rank_select.
+__device__ inline unsigned long long* late_counters(const EighBatch& e) { return (unsigned long long*)e.sel; }
+
 // ------------------------------------------------------------------ gather
 template <typename T>
 __global__ void gather_windows(EighBatch e, const T* __restrict__ At, int64_t ldat) {
@@ -105,6 +109,7 @@ __global__ void gather_windows(EighBatch e, const T* __restrict__ At, int64_t ld
     B[idx] = v;
     U[idx] = (r == c) ? 1.0 : 0.0;
   }
+  if (blockIdx.x == 0 && p == 0 && threadIdx.x < 2) late_counters(e)[threadIdx.x] = 0;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     e.state[2 * p] = 0;      // last sweep that rotated (1-based)
     e.state[2 * p + 1] = 1;  // last sweep to run: the first one always does
@@ -239,7 +244,8 @@ struct SolveLds {
 // product step against 33 us for each Jacobi sweep of the 64 x 64 problem.
 // A Jacobi sweep whose rotations were all below FINISH_ANGLE also hands over:
 // its normalised columns (given in L.X, start set) are off by about the square
-// of that.
+// of that.  It does so once: where levels cluster, Newton may refuse after
+// every sweep (eight levels at order 1024: 280 us a pair problem instead of 170).
 constexpr double NEWTON_MAX = 0.00390625;            // 2^-8
 constexpr double NEWTON_DONE = 9.313225746154785e-10;  // 2^-30
 constexpr double FINISH_ANGLE = 0.03125;             // 2^-5
@@ -617,7 +623,7 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<
       break;
     }
     if constexpr (NEWTON) {
-      if (!wide) {
+      if (!wide && !start) {
         exact_norms();
         const double iT0 = rsq_d(nT0), iT1 = rsq_d(nT1), iB0 = rsq_d(nB0), iB1 = rsq_d(nB1);
         __syncthreads();  // the norms have been read; X takes their place
@@ -875,40 +881,85 @@ __global__ __launch_bounds__(PS_NT, NEWTON ? 2 : 3) void pair_solve_apply_u(Eigh
   }
 }
 
-// The sweeps from `sweep` on, one workgroup per submatrix doing all of its
-// tiles in turn: a single launch that returns at once in the usual case.  It
-// is some ten times slower per sweep than the launches above, so it stands
-// behind enough of those (see eigh_run) that only start vectors
-// far from any the method is meant for reach it.
-template <bool NEWTON> __global__ __launch_bounds__(PS_NT, 2) void sweeps_left(EighBatch e, int sweep, int max_sweeps) {
+// The sweeps from `first` on in one launch, which returns at once in the usual
+// case that no submatrix needs them.  Its workgroups take tasks by ticket, in
+// order: for each sweep the scan, then for each round the pair problems and
+// the tiles.  A task waits until all tasks of the phases before its own are
+// done; those have lower tickets, so they are done or with running workgroups
+// that wait only on still lower ones: every wait ends however many workgroups
+// are resident.  A sweep that no submatrix runs ends the work; its tasks after
+// the scan are never done, so a workgroup waits for a sweep's scan and looks
+// whether the sweep runs before it waits for anything later.  All threads
+// release their stores before a task counts as done and acquire after a wait
+// (the XCDs' L2s are not coherent).  A round takes about what its launches
+// take; one workgroup for a whole submatrix took eight times as long (full
+// diagonalisation at order 1024 of a matrix of eight levels, 26 sweeps:
+// 1245 -> 185 ms).
+constexpr int SL_NWG = 512;    // workgroups, and tasks of a round's tiles at most
+constexpr int SL_SCAN = 32;    // scan tasks per submatrix
+template <bool NEWTON> __global__ __launch_bounds__(PS_NT, 2) void sweeps_left(EighBatch e, int first, int max_sweeps) {
   __shared__ union {
     PairLds<NEWTON> solve;
     double T[B2][LS];
   } L;
-  const int p = blockIdx.x, npairs = e.nb / 2;
-  if (!sweep_active(e, p, sweep - 1) || e.state[2 * p] != sweep) return;
-  int ran = sweep, rotated = sweep;
-  for (; sweep < max_sweeps && rotated == sweep; ++sweep) {
-    if (!__syncthreads_or(scan_columns(e, p, 0, 1))) break;
-    ran = sweep + 1;
-    for (int round = 0; round < e.nb - 1; ++round) {
-      for (int k = 0; k < npairs; ++k) {
-        if (solve_pair<NEWTON>(e, round, p, k, L.solve)) rotated = sweep + 1;
-        __syncthreads();
-      }
-      for (int w = 0; w < npairs * (npairs + 1) / 2; ++w) {
-        apply_b_tile<PS_NT>(e, round, p, w, L.T);
-        __syncthreads();
-      }
-      for (int w = 0; w < (e.Mp / B2) * npairs; ++w) {
-        apply_u_tile<PS_NT>(e, round, p, w, L.T);
-        __syncthreads();
+  __shared__ unsigned long long taken;
+  typedef unsigned long long u64;
+  const int npairs = e.nb / 2, ntri = npairs * (npairs + 1) / 2, per_u = (e.Mp / B2) * npairs;
+  const int nscan = e.P * SL_SCAN, nsolve = e.P * npairs, nb_tiles = e.P * ntri, ntiles = nb_tiles + e.P * per_u;
+  const int nwork = ntiles < SL_NWG ? ntiles : SL_NWG, nround = nsolve + nwork;
+  const u64 nsweep = nscan + (u64)(e.nb - 1) * nround;
+  // one submatrix whose sweep first - 1 rotated is enough to start
+  int left = 0;
+  for (int p = threadIdx.x; p < e.P; p += PS_NT) left |= sweep_active(e, p, first - 1) && e.state[2 * p] == first;
+  if (!__syncthreads_or(left)) return;
+  u64* count = late_counters(e);
+  auto wait = [&](u64 done) {
+    if (threadIdx.x == 0)
+      while (__hip_atomic_load(&count[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < done) __builtin_amdgcn_s_sleep(2);
+    __syncthreads();
+    __threadfence();
+  };
+  int runs = first;  // sweeps below this one are known to run
+  for (;;) {
+    if (threadIdx.x == 0) taken = atomicAdd(&count[0], 1ull);
+    __syncthreads();
+    const u64 ticket = taken, start = ticket / nsweep * nsweep;  // the sweep's first ticket
+    if (ticket / nsweep >= (u64)(max_sweeps - first)) return;
+    const int sweep = first + (int)(ticket / nsweep);
+    int t = (int)(ticket - start);
+    const bool scan = t < nscan;
+    for (; runs < sweep + (scan ? 0 : 1); ++runs) {
+      wait((u64)(runs - first) * nsweep + nscan);
+      int on = 0;
+      for (int p = threadIdx.x; p < e.P; p += PS_NT) on |= e.state[2 * p + 1] > runs;
+      if (!__syncthreads_or(on)) return;
+    }
+    if (scan) {
+      wait(start);
+      const int p = t / SL_SCAN;
+      if (sweep_active(e, p, sweep - 1) && e.state[2 * p] == sweep && scan_columns(e, p, t % SL_SCAN, SL_SCAN))
+        atomicMax(&e.state[2 * p + 1], sweep + 1);
+    } else {
+      t -= nscan;
+      const int round = t / nround;
+      t -= round * nround;
+      const bool solve = t < nsolve;
+      wait(start + nscan + (u64)round * nround + (solve ? 0 : nsolve));
+      if (solve) {
+        solve_block<NEWTON>(e, sweep, round, t, L.solve);
+      } else {
+        for (int w = t - nsolve; w < ntiles; w += nwork) {
+          const int u = w - nb_tiles, p = u < 0 ? w / ntri : u / per_u;
+          if (!sweep_active(e, p, sweep)) continue;
+          if (u < 0) apply_b_tile<PS_NT>(e, round, p, w % ntri, L.T);
+          else apply_u_tile<PS_NT>(e, round, p, u % per_u, L.T);
+          __syncthreads();
+        }
       }
     }
-  }
-  if (threadIdx.x == 0) {
-    e.state[2 * p] = rotated;
-    e.state[2 * p + 1] = ran;
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(&count[1], 1ull);
   }
 }
 
@@ -1007,7 +1058,7 @@ static hipError_t eigh_run(const EighBatch& e, const T* At, int64_t ldat, int ma
     }
   }
   if (spread < max_sweeps)
-    hipLaunchKernelGGL(sweeps_left<NEWTON>, dim3(e.P), dim3(PS_NT), 0, s, e, spread, max_sweeps);
+    hipLaunchKernelGGL(sweeps_left<NEWTON>, dim3(SL_NWG), dim3(PS_NT), 0, s, e, spread, max_sweeps);
   hipLaunchKernelGGL(rank_select, dim3(e.P, e.Mp / RS_N), dim3(RS_N * RS_W), e.Mp * sizeof(double), s, e, max_sweeps);
   return hipGetLastError();
 }

@@ -74,6 +74,28 @@ def test_full_diag_equal_diagonal(pf, n):
     assert np.max(np.abs(A @ V - V * lam)) <= 1e-12
 
 
+@pytest.mark.parametrize("n", [256, 500])
+def test_late_sweeps_clustered(pf, n):
+    """Eight levels of equal eigenvalues keep a single submatrix rotating past
+    the sixteen sweeps with their own launches, so that the launch behind them
+    spreads several sweeps over its workgroups.  Norm 7: an eigenvalue is off by
+    at most about n u 7 (4e-13), entries of the residual and of V^T V - I by
+    less; bound 1e-12 as above, times 7 where the norm enters."""
+    dev = torch.device("cuda:0")
+    g = np.random.default_rng(n)
+    Q, _ = np.linalg.qr(g.standard_normal((n, n)))
+    levels = np.sort(np.arange(n) % 8).astype(float)
+    A = (Q * levels) @ Q.T
+    A = (A + A.T) / 2
+    full = pf.FullDiag(n)
+    lam, V = full.solve(torch.from_numpy(A).to(dev))
+    assert full.plan.debug_stats()["converged_sweep"][0] > 16
+    lam, V = lam.cpu().numpy(), V.cpu().numpy()
+    assert np.max(np.abs(lam - levels)) <= 7e-12
+    assert np.max(np.abs(V.T @ V - np.eye(n))) <= 1e-12
+    assert np.max(np.abs(A @ V - V * lam)) <= 7e-12
+
+
 @pytest.mark.parametrize("n,precision,tol", [(130, "fp64", 1e-12), (200, "fp64", 1e-12), (200, "mixed_bf16", 1e-8)])
 def test_late_sweeps(pf, n, precision, tol):
     """Submatrices that need more sweeps than are enqueued round by round (two
