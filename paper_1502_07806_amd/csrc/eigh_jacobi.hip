@@ -635,6 +635,7 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<
           X[row0 + m][62 - 2 * j] = B1[m] * iB1;
           X[row0 + m][63 - 2 * j] = B0[m] * iB0;
         }
+        __syncthreads();
         newton = start = true;
       }
     }
