@@ -884,18 +884,20 @@ __global__ __launch_bounds__(PS_NT, NEWTON ? 2 : 3) void pair_solve_apply_u(Eigh
 
 // The sweeps from `first` on in one launch, which returns at once in the usual
 // case that no submatrix needs them.  Its workgroups take tasks by ticket, in
-// order: for each sweep the scan, then for each round the pair problems and
-// the tiles.  A task waits until all tasks of the phases before its own are
+// order: for each sweep the scan and the pair problems of round 0, then for each
+// round its B tiles and the next pair problems beside its U tiles.  A task waits
+// until all tasks of the phases before its own are
 // done; those have lower tickets, so they are done or with running workgroups
 // that wait only on still lower ones: every wait ends however many workgroups
 // are resident.  A sweep that no submatrix runs ends the work; its tasks after
 // the scan are never done, so a workgroup waits for a sweep's scan and looks
-// whether the sweep runs before it waits for anything later.  All threads
-// release their stores before a task counts as done and acquire after a wait
-// (the XCDs' L2s are not coherent).  A round takes about what its launches
-// take; one workgroup for a whole submatrix took eight times as long (full
-// diagonalisation at order 1024 of a matrix of eight levels, 26 sweeps:
-// 1245 -> 185 ms).
+// whether the sweep runs before it waits for anything later.  A task's stores
+// are written back before it counts as done, and the caches invalidated after a
+// wait (the XCDs' L2s are not coherent), by one thread each: by all of them it
+// cost a third of the time.  One workgroup for a whole submatrix took eight times
+// as long (full diagonalisation at order 1024 of a matrix of eight levels, 26
+// sweeps: 1245 -> 180 ms); usual sweeps are faster in their own launches
+// (order 1024: 34 ms, all sweeps this way 58).
 constexpr int SL_NWG = 512;    // workgroups, and tasks of a round's tiles at most
 constexpr int SL_SCAN = 32;    // scan tasks per submatrix
 template <bool NEWTON> __global__ __launch_bounds__(PS_NT, 2) void sweeps_left(EighBatch e, int first, int max_sweeps) {
@@ -906,19 +908,21 @@ template <bool NEWTON> __global__ __launch_bounds__(PS_NT, 2) void sweeps_left(E
   __shared__ unsigned long long taken;
   typedef unsigned long long u64;
   const int npairs = e.nb / 2, ntri = npairs * (npairs + 1) / 2, per_u = (e.Mp / B2) * npairs;
-  const int nscan = e.P * SL_SCAN, nsolve = e.P * npairs, nb_tiles = e.P * ntri, ntiles = nb_tiles + e.P * per_u;
-  const int nwork = ntiles < SL_NWG ? ntiles : SL_NWG, nround = nsolve + nwork;
-  const u64 nsweep = nscan + (u64)(e.nb - 1) * nround;
+  const int nscan = e.P * SL_SCAN, nsolve = e.P * npairs, nb_tiles = e.P * ntri, nu_tiles = e.P * per_u;
+  const int nbt = nb_tiles < SL_NWG ? nb_tiles : SL_NWG, nut = nu_tiles < SL_NWG ? nu_tiles : SL_NWG;
+  const int nround = nbt + nsolve + nut;  // tasks of a round: its B tiles, then the next pair problems beside its U tiles
+  const u64 nsweep = nscan + (u64)(e.nb - 1) * nround;  // the first pair problems take the place of the last round's
   // one submatrix whose sweep first - 1 rotated is enough to start
   int left = 0;
   for (int p = threadIdx.x; p < e.P; p += PS_NT) left |= sweep_active(e, p, first - 1) && e.state[2 * p] == first;
   if (!__syncthreads_or(left)) return;
   u64* count = late_counters(e);
   auto wait = [&](u64 done) {
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0) {
       while (__hip_atomic_load(&count[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < done) __builtin_amdgcn_s_sleep(2);
+      __threadfence();
+    }
     __syncthreads();
-    __threadfence();
   };
   int runs = first;  // sweeps below this one are known to run
   for (;;) {
@@ -941,26 +945,38 @@ template <bool NEWTON> __global__ __launch_bounds__(PS_NT, 2) void sweeps_left(E
       if (sweep_active(e, p, sweep - 1) && e.state[2 * p] == sweep && scan_columns(e, p, t % SL_SCAN, SL_SCAN))
         atomicMax(&e.state[2 * p + 1], sweep + 1);
     } else {
-      t -= nscan;
-      const int round = t / nround;
-      t -= round * nround;
-      const bool solve = t < nsolve;
-      wait(start + nscan + (u64)round * nround + (solve ? 0 : nsolve));
-      if (solve) {
-        solve_block<NEWTON>(e, sweep, round, t, L.solve);
+      t -= nscan + nsolve;  // below 0: the pair problems of round 0
+      const int round = t < 0 ? 0 : t / nround;
+      const u64 phase = start + nscan + nsolve + (u64)round * nround;  // first ticket of the round's B tiles
+      const int nnext = round + 2 < e.nb ? nsolve : 0;
+      const bool start_round = t < 0;
+      if (!start_round) t -= round * nround;
+      if (start_round || (t >= nbt && t < nbt + nnext)) {
+        wait(start_round ? start + nscan : phase + nbt);
+        solve_block<NEWTON>(e, sweep, start_round ? 0 : round + 1, start_round ? t + nsolve : t - nbt, L.solve);
+      } else if (t < nbt) {
+        wait(phase);
+        for (int w = t; w < nb_tiles; w += nbt) {
+          if (!sweep_active(e, w / ntri, sweep)) continue;
+          apply_b_tile<PS_NT>(e, round, w / ntri, w % ntri, L.T);
+          __syncthreads();
+        }
       } else {
-        for (int w = t - nsolve; w < ntiles; w += nwork) {
-          const int u = w - nb_tiles, p = u < 0 ? w / ntri : u / per_u;
-          if (!sweep_active(e, p, sweep)) continue;
-          if (u < 0) apply_b_tile<PS_NT>(e, round, p, w % ntri, L.T);
-          else apply_u_tile<PS_NT>(e, round, p, u % per_u, L.T);
+        wait(phase + nbt);
+        for (int w = t - nbt - nnext; w < nu_tiles; w += nut) {
+          if (!sweep_active(e, w / per_u, sweep)) continue;
+          apply_u_tile<PS_NT>(e, round, w / per_u, w % per_u, L.T);
           __syncthreads();
         }
       }
     }
-    __threadfence();
+    // every wave's stores have left for the L2 before one thread writes it back
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(&count[1], 1ull);
+    if (threadIdx.x == 0) {
+      __threadfence();
+      atomicAdd(&count[1], 1ull);
+    }
   }
 }
 
