@@ -27,6 +27,7 @@ struct EighBatch {
   int nb;                  // Mp / b (even)
   int inner_max_sweeps;    // sweeps of the in-LDS pair solver
   double floor_rel;        // rotation floor relative to the Gershgorin bound (0: the FP64 rounding floor)
+  int quick_sweeps;        // sweeps whose pair problems stop early (set by the run)
   double angle;            // pair-problem stopping rotation |sin| (0: the FP64 one)
   double* Bw;              // [P][Mp][Mp] working matrices (column-major)
   double* Uw;              // [P][Mp][Mp] accumulated eigenvectors

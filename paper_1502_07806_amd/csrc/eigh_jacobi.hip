@@ -157,6 +157,7 @@ __device__ inline int lo_d(double v) { return (int)__double_as_longlong(v); }
 __device__ inline int hi_d(double v) { return (int)(__double_as_longlong(v) >> 32); }
 __device__ inline double mk_d(int lo, int hi) { return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo); }
 constexpr int DPP_FROM_RIGHT = 0x101;  // row_shl:1: lane l takes lane l + 1 of its row, lane 15 keeps `old`
+constexpr int DPP_ROTATE = 0x12f;      // row_ror:15: lane l takes lane l + 1 of its row, lane 15 lane 0
 constexpr int DPP_FROM_LEFT = 0x111;   // row_shr:1: lane l takes lane l - 1 of its row, lane 0 keeps `old`
 template <int CTRL> __device__ inline double dpp_d(double old, double v) {
   return mk_d(__builtin_amdgcn_update_dpp(lo_d(old), lo_d(v), CTRL, 0xf, 0xf, false),
@@ -255,7 +256,8 @@ struct NewtonLds {
   double Y[B2][LS];
   double lam[B2];
 };
-__device__ bool newton_pair(const double* B, int Mp, int I, int J, double fl, double* Rg, NewtonLds& L, bool start) {
+__device__ __attribute__((always_inline)) inline bool newton_pair(const double* B, int Mp, int I, int J, double fl,
+                                                                  double* Rg, NewtonLds& L, bool start) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l16 = lane & 15, lq = lane >> 4;
   const int i0 = (wave & 1) * 32, j0 = (wave >> 1) * 32;  // this wave's quadrant
@@ -438,8 +440,18 @@ template <> struct PairLds<true> {
 // Pair problem k of submatrix p in the given round (PS_NT threads); whether it
 // rotated.  NEWTON: try newton_pair first (the FP64 path; the mixed path stops
 // its sweeps at a looser angle).
-template <bool NEWTON>
-__device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<NEWTON>& PL) {
+//
+// quick (compiled in with QUICK, which costs registers): one sweep only, and
+// past round 0, whose full tournament has rotated inside every block, only over
+// the 32 x 32 pairs with one column in each block: the top columns stay, the
+// bottom ones turn by one position a round, 32 rounds.  W's columns are not yet
+// orthogonal then, so R is the product of the rotations.  Far from convergence
+// the outer sweeps reach no further with the pair problems solved to the end:
+// full diagonalisation at order 1024 takes 11 sweeps of 26 us a round instead of
+// 10 of 130 us (34.3 -> 17.6 ms), and 23 instead of 26 where eight levels
+// cluster (171 -> 69 ms).
+template <bool NEWTON, bool QUICK>
+__device__ bool solve_pair(const EighBatch& e, int round, int p, int k, bool quick, PairLds<NEWTON>& PL) {
   SolveLds& L = PL.jacobi;
   const int npairs = e.nb / 2;
   int* flagR = flag_buf(e, round) + (int64_t)p * npairs + k;
@@ -539,6 +551,43 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<
     t1 = nt1;
   };
   const double angle = e.angle > 0.0 ? e.angle : ANGLE;
+  // quick: the product of the rotations, held as W is
+  double QT0[PS_R], QT1[PS_R], QB0[PS_R], QB1[PS_R];
+  if constexpr (QUICK) {
+#pragma unroll
+    for (int m = 0; m < PS_R; ++m) {
+      QT0[m] = row0 + m == 2 * j ? 1.0 : 0.0;
+      QT1[m] = row0 + m == 2 * j + 1 ? 1.0 : 0.0;
+      QB1[m] = row0 + m == 62 - 2 * j ? 1.0 : 0.0;
+      QB0[m] = row0 + m == 63 - 2 * j ? 1.0 : 0.0;
+    }
+  }
+  const bool cross = QUICK && quick && round > 0;
+  const int turns = cross ? B2 / 2 : B2 - 1;
+  auto turn = [&](double& b0, double& b1) {
+    const double n1 = dpp_d<DPP_ROTATE>(b0, b0);
+    b0 = b1;
+    b1 = n1;
+  };
+  auto store_rotation = [&](const double (&t0)[PS_R], const double (&t1)[PS_R], const double (&b0)[PS_R],
+                            const double (&b1)[PS_R], double iT0, double iT1, double iB0, double iB1) {
+#pragma unroll
+    for (int m = 0; m < PS_R; ++m) {
+      *(double2*)&Rg[(row0 + m) * B2 + 2 * j] = make_double2(t0[m] * iT0, t1[m] * iT1);
+      *(double2*)&Rg[(row0 + m) * B2 + 62 - 2 * j] = make_double2(b1[m] * iB1, b0[m] * iB0);
+    }
+  };
+  auto hand_over = [&](const double (&t0)[PS_R], const double (&t1)[PS_R], const double (&b0)[PS_R],
+                       const double (&b1)[PS_R], double iT0, double iT1, double iB0, double iB1) {
+    double (*X)[LS] = PL.newton().X;
+#pragma unroll
+    for (int m = 0; m < PS_R; ++m) {
+      X[row0 + m][2 * j] = t0[m] * iT0;
+      X[row0 + m][2 * j + 1] = t1[m] * iT1;
+      X[row0 + m][62 - 2 * j] = b1[m] * iB1;
+      X[row0 + m][63 - 2 * j] = b0[m] * iB0;
+    }
+  };
   bool converged = false;
   int par = 0;
   bool newton = NEWTON && !__syncthreads_or(far), start = false;
@@ -552,6 +601,10 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<
           }
           return true;
         }
+        if (QUICK && quick && start) {  // the rotation stored at the hand-over stands
+          converged = true;
+          break;
+        }
         newton = false;
         __syncthreads();  // the sweeps reuse its LDS
       }
@@ -559,7 +612,7 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<
     unsigned long long big = 0, wide = 0;  // lanes that rotated by more than the stopping / finishing angle
     exact_norms();
 #pragma unroll 1
-    for (int r = 0; r < B2 - 1; ++r) {
+    for (int r = 0; r < turns; ++r) {
       double p0 = 0.0, p1 = 0.0;
 #pragma unroll
       for (int m = 0; m < PS_R; ++m) {
@@ -590,7 +643,7 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<
       bool pos = d > 0.0;
       if (__ballot(d == 0.0)) {  // equal norms: the column of lower index takes the minus sign
         const int it = slot == 0 ? 0 : (slot - 1 + r) % (B2 - 1) + 1, ib = (62 - slot + r) % (B2 - 1) + 1;
-        if (d == 0.0) pos = it < ib;
+        if (d == 0.0) pos = cross || it < ib;
       }
       double s0 = (pos ? ab : -ab) * ir * ic, c0 = h * ic;
       c0 = rot ? c0 : 1.0;
@@ -607,15 +660,24 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<
       nB0 += x0;
       nT1 -= x1;
       nB1 += x1;
-      move(nT0, nB0, nT1, nB1);
+      auto rotate = [&](double& t0, double& t1, double& b0, double& b1) {
+        const double t0o = t0, b0o = b0, t1o = t1, b1o = b1;
+        t0 = fma(-s0, b0o, c0 * t0o);
+        b0 = fma(s0, t0o, c0 * b0o);
+        t1 = fma(-s1, b1o, c1 * t1o);
+        b1 = fma(s1, t1o, c1 * b1o);
+        if (cross) turn(b0, b1);
+        else move(t0, b0, t1, b1);
+      };
+      if (cross) turn(nB0, nB1);
+      else move(nT0, nB0, nT1, nB1);
 #pragma unroll
-      for (int m = 0; m < PS_R; ++m) {
-        const double t0 = T0[m], b0 = B0[m], t1 = T1[m], b1 = B1[m];
-        T0[m] = fma(-s0, b0, c0 * t0);
-        B0[m] = fma(s0, t0, c0 * b0);
-        T1[m] = fma(-s1, b1, c1 * t1);
-        B1[m] = fma(s1, t1, c1 * b1);
-        move(T0[m], B0[m], T1[m], B1[m]);
+      for (int m = 0; m < PS_R; ++m) rotate(T0[m], T1[m], B0[m], B1[m]);
+      if constexpr (QUICK) {
+        if (quick) {
+#pragma unroll
+          for (int m = 0; m < PS_R; ++m) rotate(QT0[m], QT1[m], QB0[m], QB1[m]);
+        }
       }
     }
     if (!big) {
@@ -624,19 +686,19 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<
     }
     if constexpr (NEWTON) {
       if (!wide && !start) {
-        exact_norms();
-        const double iT0 = rsq_d(nT0), iT1 = rsq_d(nT1), iB0 = rsq_d(nB0), iB1 = rsq_d(nB1);
-        __syncthreads();  // the norms have been read; X takes their place
-        double (*X)[LS] = PL.newton().X;
-#pragma unroll
-        for (int m = 0; m < PS_R; ++m) {
-          X[row0 + m][2 * j] = T0[m] * iT0;
-          X[row0 + m][2 * j + 1] = T1[m] * iT1;
-          X[row0 + m][62 - 2 * j] = B1[m] * iB1;
-          X[row0 + m][63 - 2 * j] = B0[m] * iB0;
+        if (QUICK && quick) {
+          store_rotation(QT0, QT1, QB0, QB1, 1.0, 1.0, 1.0, 1.0);  // stands if Newton refuses
+          hand_over(QT0, QT1, QB0, QB1, 1.0, 1.0, 1.0, 1.0);
+        } else {
+          exact_norms();
+          __syncthreads();  // the norms have been read; X takes their place
+          hand_over(T0, T1, B0, B1, rsq_d(nT0), rsq_d(nT1), rsq_d(nB0), rsq_d(nB1));
         }
         __syncthreads();
         newton = start = true;
+      } else if (QUICK && quick) {
+        converged = true;
+        break;
       }
     }
   }
@@ -646,12 +708,11 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<
   int* inf = info_of(e, p);
   if (!converged && threadIdx.x == 0 && inf) atomicCAS(inf, 0, PFSM_INFO_EIGH_NOCONV);
   // eigenvectors: normalised columns of W, row-major: Rg[r * 2b + c] = R(r, c)
-  exact_norms();
-  const double iT0 = rsq_d(nT0), iT1 = rsq_d(nT1), iB0 = rsq_d(nB0), iB1 = rsq_d(nB1);
-#pragma unroll
-  for (int m = 0; m < PS_R; ++m) {
-    *(double2*)&Rg[(row0 + m) * B2 + 2 * j] = make_double2(T0[m] * iT0, T1[m] * iT1);
-    *(double2*)&Rg[(row0 + m) * B2 + 62 - 2 * j] = make_double2(B1[m] * iB1, B0[m] * iB0);
+  if (QUICK && quick) {
+    if (!start) store_rotation(QT0, QT1, QB0, QB1, 1.0, 1.0, 1.0, 1.0);
+  } else {
+    exact_norms();
+    store_rotation(T0, T1, B0, B1, rsq_d(nT0), rsq_d(nT1), rsq_d(nB0), rsq_d(nB1));
   }
   if (threadIdx.x == 0) {
     *flagR = 1;
@@ -660,16 +721,16 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, PairLds<
   return true;
 }
 
-template <bool NEWTON>
+template <bool NEWTON, bool QUICK>
 __device__ inline void solve_block(const EighBatch& e, int sweep, int round, int b, PairLds<NEWTON>& L) {
   const int npairs = e.nb / 2, p = b / npairs;
   if (!sweep_active(e, p, sweep)) return;
-  if (solve_pair<NEWTON>(e, round, p, b % npairs, L) && threadIdx.x == 0) atomicMax(&e.state[2 * p], sweep + 1);
+  if (solve_pair<NEWTON, QUICK>(e, round, p, b % npairs, QUICK && sweep < e.quick_sweeps, L) && threadIdx.x == 0) atomicMax(&e.state[2 * p], sweep + 1);
 }
 
-template <bool NEWTON> __global__ __launch_bounds__(PS_NT, 2) void pair_solve(EighBatch e, int sweep) {
+template <bool NEWTON, bool QUICK> __global__ __launch_bounds__(PS_NT, 2) void pair_solve(EighBatch e, int sweep) {
   __shared__ PairLds<NEWTON> L;
-  solve_block<NEWTON>(e, sweep, 0, blockIdx.x, L);
+  solve_block<NEWTON, QUICK>(e, sweep, 0, blockIdx.x, L);
 }
 
 // 64x64x64 products with FP64 MFMA by NTH / 64 waves: wave w owns rows
@@ -865,7 +926,7 @@ __global__ __launch_bounds__(AB_NT) void pair_apply_b(EighBatch e, int sweep, in
 
 // The pair problems of round solve_round (the first P * npairs workgroups;
 // none when solve_round < 0) beside the U tiles of round u_round (the rest).
-template <bool NEWTON>
+template <bool NEWTON, bool QUICK>
 __global__ __launch_bounds__(PS_NT, NEWTON ? 2 : 3) void pair_solve_apply_u(EighBatch e, int sweep, int solve_round, int u_round) {
   __shared__ union {
     PairLds<NEWTON> solve;
@@ -875,7 +936,7 @@ __global__ __launch_bounds__(PS_NT, NEWTON ? 2 : 3) void pair_solve_apply_u(Eigh
   const int ns = solve_round >= 0 ? e.P * npairs : 0;
   const int b = blockIdx.x;
   if (b < ns) {
-    solve_block<NEWTON>(e, sweep, solve_round, b, L.solve);
+    solve_block<NEWTON, QUICK>(e, sweep, solve_round, b, L.solve);
   } else {
     const int per = (e.Mp / B2) * npairs, p = (b - ns) / per;
     if (sweep_active(e, p, sweep)) apply_u_tile<PS_NT>(e, u_round, p, (b - ns) % per, L.T);
@@ -900,7 +961,8 @@ __global__ __launch_bounds__(PS_NT, NEWTON ? 2 : 3) void pair_solve_apply_u(Eigh
 // (order 1024: 34 ms, all sweeps this way 58).
 constexpr int SL_NWG = 512;    // workgroups, and tasks of a round's tiles at most
 constexpr int SL_SCAN = 32;    // scan tasks per submatrix
-template <bool NEWTON> __global__ __launch_bounds__(PS_NT, 2) void sweeps_left(EighBatch e, int first, int max_sweeps) {
+template <bool NEWTON, bool QUICK>
+__global__ __launch_bounds__(PS_NT, 2) void sweeps_left(EighBatch e, int first, int max_sweeps) {
   __shared__ union {
     PairLds<NEWTON> solve;
     double T[B2][LS];
@@ -953,7 +1015,7 @@ template <bool NEWTON> __global__ __launch_bounds__(PS_NT, 2) void sweeps_left(E
       if (!start_round) t -= round * nround;
       if (start_round || (t >= nbt && t < nbt + nnext)) {
         wait(start_round ? start + nscan : phase + nbt);
-        solve_block<NEWTON>(e, sweep, start_round ? 0 : round + 1, start_round ? t + nsolve : t - nbt, L.solve);
+        solve_block<NEWTON, QUICK>(e, sweep, start_round ? 0 : round + 1, start_round ? t + nsolve : t - nbt, L.solve);
       } else if (t < nbt) {
         wait(phase);
         for (int w = t; w < nb_tiles; w += nbt) {
@@ -1046,8 +1108,15 @@ __global__ void embed_x0(EighBatch e, T* __restrict__ X, int64_t ldx, double* __
 
 }  // namespace
 
-template <bool NEWTON, typename T>
-static hipError_t eigh_run(const EighBatch& e, const T* At, int64_t ldat, int max_sweeps, hipStream_t s) {
+// The last EXACT_SWEEPS sweeps of the limit solve their pair problems to the
+// end, as sweeps near convergence do anyway (Newton's iteration): below order
+// 256 clustered levels take up to twice the sweeps of quick ones, so a limit
+// near the usual count (the default, 10) is left as it was.
+constexpr int EXACT_SWEEPS = 12;
+template <bool NEWTON, bool QUICK, typename T>
+static hipError_t eigh_run(const EighBatch& batch, const T* At, int64_t ldat, int max_sweeps, hipStream_t s) {
+  EighBatch e = batch;
+  e.quick_sweeps = max_sweeps - EXACT_SWEEPS;
   const int npairs = e.nb / 2;
   const int nrc = e.Mp / B2;
   {
@@ -1066,16 +1135,16 @@ static hipError_t eigh_run(const EighBatch& e, const T* At, int64_t ldat, int ma
     if (sw > 0) hipLaunchKernelGGL(sweep_scan, dim3(std::min(e.Mp, 64), e.P), dim3(256), 0, s, e, sw);
     // round r: B tiles, then the next round's pair problems beside the U tiles
     const int rounds = e.nb - 1;
-    hipLaunchKernelGGL(pair_solve<NEWTON>, dim3(e.P * npairs), dim3(PS_NT), 0, s, e, sw);
+    hipLaunchKernelGGL((pair_solve<NEWTON, QUICK>), dim3(e.P * npairs), dim3(PS_NT), 0, s, e, sw);
     for (int r = 0; r < rounds; ++r) {
       hipLaunchKernelGGL(pair_apply_b, dim3(e.P * (npairs * (npairs + 1) / 2)), dim3(AB_NT), 0, s, e, sw, r);
       const int next = r + 1 < rounds ? r + 1 : -1;
       const unsigned grid = (unsigned)((next >= 0 ? e.P * npairs : 0) + e.P * nrc * npairs);
-      hipLaunchKernelGGL(pair_solve_apply_u<NEWTON>, dim3(grid), dim3(PS_NT), 0, s, e, sw, next, r);
+      hipLaunchKernelGGL((pair_solve_apply_u<NEWTON, QUICK>), dim3(grid), dim3(PS_NT), 0, s, e, sw, next, r);
     }
   }
   if (spread < max_sweeps)
-    hipLaunchKernelGGL(sweeps_left<NEWTON>, dim3(SL_NWG), dim3(PS_NT), 0, s, e, spread, max_sweeps);
+    hipLaunchKernelGGL((sweeps_left<NEWTON, QUICK>), dim3(SL_NWG), dim3(PS_NT), 0, s, e, spread, max_sweeps);
   hipLaunchKernelGGL(rank_select, dim3(e.P, e.Mp / RS_N), dim3(RS_N * RS_W), e.Mp * sizeof(double), s, e, max_sweeps);
   return hipGetLastError();
 }
@@ -1083,7 +1152,9 @@ static hipError_t eigh_run(const EighBatch& e, const T* At, int64_t ldat, int ma
 // The FP64 path is the one with the FP64 rotation floor.
 template <typename T>
 static hipError_t eigh_any(const EighBatch& e, const T* At, int64_t ldat, int max_sweeps, hipStream_t s) {
-  return e.floor_rel > 0.0 ? eigh_run<false>(e, At, ldat, max_sweeps, s) : eigh_run<true>(e, At, ldat, max_sweeps, s);
+  if (e.floor_rel > 0.0) return eigh_run<false, false>(e, At, ldat, max_sweeps, s);
+  return max_sweeps > EXACT_SWEEPS ? eigh_run<true, true>(e, At, ldat, max_sweeps, s)
+                                   : eigh_run<true, false>(e, At, ldat, max_sweeps, s);
 }
 
 hipError_t eigh_batched_run(const EighBatch& e, const double* At, int64_t ldat, int max_sweeps, hipStream_t s) {

@@ -96,6 +96,21 @@ def test_late_sweeps_clustered(pf, n):
     assert np.max(np.abs(A @ V - V * lam)) <= 7e-12
 
 
+@pytest.mark.parametrize("max_sweeps", [12, 13, 40])
+@pytest.mark.parametrize("n", [33, 64, 97, 300])
+def test_full_diag_sweep_limits(pf, n, max_sweeps):
+    """A limit of 12 solves every pair problem to the end, 13 the first sweep's
+    and 40 nearly all in one sweep over the pairs between the blocks: the same
+    eigenpairs, with the bounds of the equal-diagonal test (norm 2 here)."""
+    dev = torch.device("cuda:0")
+    A = _random_symmetric(n, n) / np.sqrt(n)
+    lam, V = pf.FullDiag(n, max_sweeps).solve(torch.from_numpy(A).to(dev))
+    lam, V = lam.cpu().numpy(), V.cpu().numpy()
+    assert np.max(np.abs(lam - np.linalg.eigvalsh(A))) <= 1e-12
+    assert np.max(np.abs(V.T @ V - np.eye(n))) <= 1e-12
+    assert np.max(np.abs(A @ V - V * lam)) <= 1e-12
+
+
 @pytest.mark.parametrize("n,precision,tol", [(130, "fp64", 1e-12), (200, "fp64", 1e-12), (200, "mixed_bf16", 1e-8)])
 def test_late_sweeps(pf, n, precision, tol):
     """Submatrices that need more sweeps than are enqueued round by round (two
