@@ -30,7 +30,8 @@ constexpr int TILE = BM * ROWB;      // 36864 bytes per operand per stage
 //   CFG 5: all weight groups at once from one staging of every plane
 //          (gemm_oz_multi; 128 x 128 block tiles, 8 waves of 64 x 32, a
 //          four-slot ring of 32-byte k stages), s = 3 .. 5
-//   CFG 6: CFG 5 with a two-slot ring of 64-byte k stages (the default)
+//   CFG 6: CFG 5 with a two-slot ring of 64-byte k stages (the default); small
+//          products in tiles of 64 x 64, 4 waves, three slots
 // The per-group kernels keep the running sum in C (read-modify-write per
 // launch); the fused kernel pays that launch and epilogue cost once per tile.
 template <int CFG> struct OzCfg;
@@ -577,23 +578,27 @@ __global__ __launch_bounds__(NT, 1) void gemm_oz_fused(OzArgs a, int tiles_m, in
 // added in FP64 at the end, smallest weights first: the same additions in the
 // same order as the fused kernel's store and atomic adds, so C is the same bit
 // for bit, and it is written once.
-constexpr int MT = 128;
+// Small products take block tiles of 64 x 64 with four waves of 32 x 32 instead:
+// of order 607, 25 tiles of 128 left nine CUs in ten idle (35 us; a mixed solve
+// 1009 -> 990 us).  An output's sums are the same.
+constexpr int MT = 128, MT_SMALL = 64;
 
 // Stage of MBK k bytes per row (32 or 64), MST = 128 KB / ... stages in the ring.
 // 32-byte rows: the two 16-byte chunks of rows 8..15 (mod 16) swap places; 64-byte
 // rows: chunk c of row r sits at c ^ dswz(r).  Either way the fragment reads of
 // 16 consecutive rows cover all 64 banks once.
 template <int MBK> __device__ inline int mswz(int r) { return MBK == 32 ? (r >> 3) & 1 : dswz(r); }
-template <int MBK> constexpr int multi_stages(int S) { return (MBK == 32 ? 4 : 2) + 0 * S; }
+template <int MBK, int T> constexpr int multi_stages() { return T == MT_SMALL ? 3 : MBK == 32 ? 4 : 2; }
 
-template <int S, int MBK>
-__global__ __launch_bounds__(512, 1) void gemm_oz_multi(OzArgs a, int tiles_m, int tiles_n) {
-  constexpr int WR = 2, WC = 1;          // 32 x 32 blocks per wave: 64 x 32
-  constexpr int MPLANE = MT * MBK;       // the k slice of one plane of one operand
-  constexpr int MST = multi_stages<MBK>(S);
+template <int S, int MBK, int T>
+__global__ __launch_bounds__(4 * T, 1) void gemm_oz_multi(OzArgs a, int tiles_m, int tiles_n) {
+  constexpr int WR = T / 64, WC = 1;     // 32 x 32 blocks per wave: 64 x 32 or 32 x 32
+  constexpr int NW = T / 16;             // waves
+  constexpr int MPLANE = T * MBK;        // the k slice of one plane of one operand
+  constexpr int MST = multi_stages<MBK, T>();
   constexpr int STAGE = 2 * S * MPLANE;  // A planes, then B planes
-  constexpr int RG = MT * MBK / 1024;    // 1 KB row groups per plane
-  constexpr int LPW = 2 * S * RG / 8;    // 1 KB loads per wave and stage
+  constexpr int RG = T * MBK / 1024;     // 1 KB row groups per plane
+  constexpr int LPW = 2 * S * RG / NW;   // 1 KB loads per wave and stage
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   int64_t m0, n0;
   {
@@ -601,21 +606,20 @@ __global__ __launch_bounds__(512, 1) void gemm_oz_multi(OzArgs a, int tiles_m, i
     const int GROUP = 4;
     const int first_m = (t / (GROUP * tiles_n)) * GROUP;
     const int gsz = min(tiles_m - first_m, GROUP);
-    m0 = (int64_t)(first_m + (t % (GROUP * tiles_n)) % gsz) * MT;
-    n0 = (int64_t)((t % (GROUP * tiles_n)) / gsz) * MT;
+    m0 = (int64_t)(first_m + (t % (GROUP * tiles_n)) % gsz) * T;
+    n0 = (int64_t)((t % (GROUP * tiles_n)) / gsz) * T;
   }
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wi0 = (wave & 1) * 64, wj0 = (wave >> 1) * 32;
+  const int wi0 = (wave & 1) * (32 * WR), wj0 = (wave >> 1) * 32;
   const int l32 = lane & 31, lh = lane >> 5;
   const int ntk = (int)(a.ldp / MBK);
-  // Wave w stages row group w % 4 (rows 32 (w % 4) .. + 31) of the planes
-  // w / 4, w / 4 + 2, ... of the list A_1 .. A_s, B_1 .. B_s: lane L holds row
-  // 32 (w % 4) + L / 2, stored chunk L % 2.  Rows past the edge read the last
+  // Planes are listed A_1 .. A_s, B_1 .. B_s.  32-byte rows: wave w stages row
+  // group w % 4 of the planes w / 4, w / 4 + 2, ..., lane L holding row
+  // 32 (w % 4) + L / 2, stored chunk L % 2; 64-byte rows: row group w of every
+  // plane, lane L holding row 16 w + L / 4.  Rows past the edge read the last
   // row (their outputs are not stored).
-  // (32-byte rows: wave w stages row group w % 4 of the planes w / 4, w / 4 + 2, ...;
-  // 64-byte rows: row group w of every plane, lane L holding row 16 w + L / 4)
-  const int rg = wave % RG, po0 = wave / RG, pstep = 8 / RG;
+  const int rg = wave % RG, po0 = wave / RG, pstep = NW / RG;
   uint32_t offA, offB;
   {
     constexpr int LPR = MBK / 16;  // lanes per row
@@ -815,15 +819,21 @@ __global__ __launch_bounds__(256) void k_oz_split(const double* X, int64_t ldx, 
 }
 
 
-template <int S, int MBK> constexpr int multi_lds() { return multi_stages<MBK>(S) * 2 * S * MT * MBK; }
-template <int S, int MBK> hipError_t oz_multi_init() {
-  return hipFuncSetAttribute((const void*)gemm_oz_multi<S, MBK>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             multi_lds<S, MBK>());
+template <int S, int MBK, int T> constexpr int multi_lds() { return multi_stages<MBK, T>() * 2 * S * T * MBK; }
+template <int S, int MBK, int T> hipError_t oz_multi_init() {
+  return hipFuncSetAttribute((const void*)gemm_oz_multi<S, MBK, T>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             multi_lds<S, MBK, T>());
 }
-template <int S, int MBK> void oz_multi_launch(const OzArgs& a, hipStream_t st) {
-  const int tm = (int)((a.M + MT - 1) / MT), tn = (int)((a.N + MT - 1) / MT);
-  constexpr int lds = multi_lds<S, MBK>();
-  hipLaunchKernelGGL((gemm_oz_multi<S, MBK>), dim3((unsigned)(tm * tn)), dim3(512), lds, st, a, tm, tn);
+template <int S, int MBK, int T> void oz_multi_launch(const OzArgs& a, hipStream_t st) {
+  const int tm = (int)((a.M + T - 1) / T), tn = (int)((a.N + T - 1) / T);
+  constexpr int lds = multi_lds<S, MBK, T>();
+  hipLaunchKernelGGL((gemm_oz_multi<S, MBK, T>), dim3((unsigned)(tm * tn)), dim3(4 * T), lds, st, a, tm, tn);
+}
+// Tiles of 64 while those of 128 leave more than half of the 256 CUs idle.
+template <int S> void oz_multi_launch64(const OzArgs& a, hipStream_t st) {
+  const int64_t tiles = ((a.M + MT - 1) / MT) * ((a.N + MT - 1) / MT);
+  if (tiles <= 128) oz_multi_launch<S, 64, MT_SMALL>(a, st);
+  else oz_multi_launch<S, 64, MT>(a, st);
 }
 
 }  // namespace
@@ -844,12 +854,15 @@ hipError_t oz_init() {
   if (e == hipSuccess)
     e = hipFuncSetAttribute((const void*)gemm_oz_fused<512, 2, 4, 2, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             DST * 2 * DTILE);
-  if (e == hipSuccess) e = oz_multi_init<3, 32>();
-  if (e == hipSuccess) e = oz_multi_init<4, 32>();
-  if (e == hipSuccess) e = oz_multi_init<5, 32>();
-  if (e == hipSuccess) e = oz_multi_init<3, 64>();
-  if (e == hipSuccess) e = oz_multi_init<4, 64>();
-  if (e == hipSuccess) e = oz_multi_init<5, 64>();
+  if (e == hipSuccess) e = oz_multi_init<3, 32, MT>();
+  if (e == hipSuccess) e = oz_multi_init<4, 32, MT>();
+  if (e == hipSuccess) e = oz_multi_init<5, 32, MT>();
+  if (e == hipSuccess) e = oz_multi_init<3, 64, MT>();
+  if (e == hipSuccess) e = oz_multi_init<3, 64, MT_SMALL>();
+  if (e == hipSuccess) e = oz_multi_init<4, 64, MT>();
+  if (e == hipSuccess) e = oz_multi_init<4, 64, MT_SMALL>();
+  if (e == hipSuccess) e = oz_multi_init<5, 64, MT>();
+  if (e == hipSuccess) e = oz_multi_init<5, 64, MT_SMALL>();
 
   return e;
 }
@@ -890,15 +903,15 @@ hipError_t gemm_oz(int64_t M, int64_t N, int64_t K, int s, const int8_t* Ap, con
     return hipGetLastError();
   }
   if (cfg == 5) {
-    if (s == 3) oz_multi_launch<3, 32>(a, st);
-    else if (s == 4) oz_multi_launch<4, 32>(a, st);
-    else oz_multi_launch<5, 32>(a, st);
+    if (s == 3) oz_multi_launch<3, 32, MT>(a, st);
+    else if (s == 4) oz_multi_launch<4, 32, MT>(a, st);
+    else oz_multi_launch<5, 32, MT>(a, st);
     return hipGetLastError();
   }
   if (cfg == 6) {
-    if (s == 3) oz_multi_launch<3, 64>(a, st);
-    else if (s == 4) oz_multi_launch<4, 64>(a, st);
-    else oz_multi_launch<5, 64>(a, st);
+    if (s == 3) oz_multi_launch64<3>(a, st);
+    else if (s == 4) oz_multi_launch64<4>(a, st);
+    else oz_multi_launch64<5>(a, st);
     return hipGetLastError();
   }
 

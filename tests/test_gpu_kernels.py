@@ -662,6 +662,26 @@ def test_gemm_oz_multi_matches_fused(dev, M, N, K, s):
     assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
 
 
+@pytest.mark.parametrize("M,N,K,s", [(1, 1, 5, 3), (64, 64, 64, 4), (65, 63, 65, 5), (1409, 1408, 130, 5),
+                                     (1408, 1409, 70, 3), (1408, 1408, 64, 4)])
+def test_gemm_oz_multi_tiles(dev, M, N, K, s):
+    """The default configuration on both sides of its change of tile (128 tiles of
+    128 x 128) and at the edges of the 64 x 64 one: bit for bit the fused kernel."""
+    g = np.random.default_rng(5 * M + N + K + s)
+    A = g.standard_normal((M, K))
+    B = g.standard_normal((K, N))
+    Ap, _, _, info_a, _, ea = _oz_split_dev(A.T, s, dev)
+    Bp, _, _, info_b, _, eb = _oz_split_dev(B, s, dev)
+    assert info_a == info_b == 0
+    out = []
+    for cfg in (4, 6):
+        C = torch.full((N, M), np.nan, dtype=torch.float64, device=dev).t()
+        assert lib().pfsm_test_gemm_oz(M, N, K, s, _p(Ap), _p(ea), _p(Bp), _p(eb), _p(C), M, cfg, _stream()) == 0
+        torch.cuda.synchronize()
+        out.append(_np(C))
+    assert np.all(np.isfinite(out[0])) and np.array_equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("n", [512, 700])
 @pytest.mark.parametrize("by_rows,flags", [(False, 32), (False, 2), (True, 32)])
 def test_pack_band_and_gated_far(dev, n, by_rows, flags):
