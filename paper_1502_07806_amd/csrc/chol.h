@@ -1,7 +1,7 @@
 #pragma once
 #include "common.h"
 namespace pfsm {
-constexpr int CHOL_NB = 64;    // diagonal block (one wavefront, registers)
+constexpr int CHOL_NB = 64;    // diagonal block (one workgroup)
 constexpr int CHOL_NB2 = 512;  // panel width between trailing updates
 // Cholesky: S (n x n, lower valid) -> L in place.  Tbuf holds ceil(n/64) blocks
 // of 64x64: the transposed inverses of the diagonal blocks of L.

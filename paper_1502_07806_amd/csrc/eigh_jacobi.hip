@@ -7,7 +7,7 @@
 //   for each sweep, for each round of a round-robin tournament over the
 //   nb = Mp/b column blocks:
 //     solve   (one workgroup per block pair (I,J)): the 2b x 2b matrix
-//             [B_II B_IJ; B_JI B_JJ] is diagonalised in LDS by a scalar
+//             [B_II B_IJ; B_JI B_JJ] is diagonalised by a scalar
 //             parallel-order cyclic Jacobi, giving an orthogonal R_IJ;
 //     apply   (one workgroup per 2b x 2b tile): B <- J^T B J and U <- U J
 //             with J = diag of the R's, as small MFMA products in LDS; the
@@ -17,7 +17,8 @@
 // (The pair problem is solved by a one-sided Jacobi, see solve_pair.)
 // Before every sweep after the first, one launch scans each submatrix for an
 // entry that has to be rotated; a submatrix without one has converged and
-// the later kernels return at once for it.  A pair (p, q) is rotated when |b_pq| > 2^-53 sqrt(|b_pp b_qq|) (relative accuracy) and
+// the later kernels return at once for it.  A pair (p, q) is rotated when
+// |b_pq| > 2^-53 sqrt(|b_pp b_qq|) (relative accuracy) and
 // |b_pq| > 256 * 2^-53 * ||B|| (rounding floor of the block products, with
 // ||B|| bounded by the Gershgorin interval of the full matrix).  Without the
 // floor, the rounding error of the MFMA block updates would keep rotating
@@ -961,6 +962,9 @@ __global__ __launch_bounds__(PS_NT, NEWTON ? 2 : 3) void pair_solve_apply_u(Eigh
 // (order 1024: 34 ms, all sweeps this way 58).
 constexpr int SL_NWG = 512;    // workgroups, and tasks of a round's tiles at most
 constexpr int SL_SCAN = 32;    // scan tasks per submatrix
+// Polls of a wait (some ten seconds) after which it reports non-convergence and
+// lets all waits through, so that even a broken order could not hang the queue.
+constexpr int SL_SPINS = 1 << 24;
 template <bool NEWTON, bool QUICK>
 __global__ __launch_bounds__(PS_NT, 2) void sweeps_left(EighBatch e, int first, int max_sweeps) {
   __shared__ union {
@@ -981,7 +985,15 @@ __global__ __launch_bounds__(PS_NT, 2) void sweeps_left(EighBatch e, int first, 
   u64* count = late_counters(e);
   auto wait = [&](u64 done) {
     if (threadIdx.x == 0) {
-      while (__hip_atomic_load(&count[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < done) __builtin_amdgcn_s_sleep(2);
+      int spins = 0;
+      while (__hip_atomic_load(&count[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < done) {
+        __builtin_amdgcn_s_sleep(2);
+        if (++spins == SL_SPINS) {
+          for (int p = 0; p < e.P; ++p)
+            if (int* inf = info_of(e, p)) atomicCAS(inf, 0, PFSM_INFO_EIGH_NOCONV);
+          atomicMax(&count[1], 1ull << 62);
+        }
+      }
       __threadfence();
     }
     __syncthreads();
