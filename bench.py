@@ -165,7 +165,7 @@ def bench_g2s(n: int, args, iterations: int = 8):
             "residual_first_last": [float(r[0]), float(r[-1])],
             "roofline": {"bound": "mfma", "achieved": fl / (step_ms * 1e-3) / 1e12, "peak": PEAK_TFLOPS["fp64"],
                          "unit": "TFLOP/s", "frac": fl / (step_ms * 1e-3) / 1e12 / PEAK_TFLOPS["fp64"],
-                         "kernel": "gemm_f64_kernel<T,N,EPI_G2S> (one per step; step time includes a residual "
+                         "kernel": "gemm_f64_dl<T,N,EPI_G2S> (one per step; step time includes a residual "
                                    "reduction launch)"}}
 
 

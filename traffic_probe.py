@@ -68,7 +68,7 @@ def summarize(fetch_csv: str, write_csv: str, n: int, out: str):
                                     "by what the same counter reads for a 1 GiB device copy"}}
     for key, name in (("gemm_x3_fsupd_n%d" % n, "gemm_x3_dl<2, true, 3>"),
                       ("gemm_x3_fsupd_plain_n%d" % n, "gemm_x3_dl<2, true, 1>"),
-                      ("gemm_f64_fsupd_n%d" % n, "gemm_f64_kernel"), ("gemm_oz_n%d" % n, OZ_PRODUCT)):
+                      ("gemm_f64_fsupd_n%d" % n, "gemm_f64_dl"), ("gemm_oz_n%d" % n, OZ_PRODUCT)):
         f, w = pick(fe, name) * 1024 * sf, pick(wr, name) * 1024 * sw
         res[key] = {"kernel": name, "fetch_bytes": f, "write_bytes": w, "bytes_per_launch": f + w,
                     "source_hash": gemm_source_hash()}
@@ -106,10 +106,11 @@ def trace_summary(trace_csv: str, out: str):
     sweeps, cur = [], None
     for r, d in zip(seq, dur):
         name = _short(r["Kernel_Name"])
-        if name == "sweep_begin":
+        kernel = name.split("<")[0]
+        if kernel == "pair_solve":  # a sweep's first launch (its scan counts with the sweep before)
             cur = [0.0, 0]
             sweeps.append(cur)
-        if cur is not None and name in ("sweep_begin", "pair_solve", "pair_apply_b", "pair_solve_apply_u"):
+        if cur is not None and kernel in ("sweep_scan", "pair_solve", "pair_apply_b", "pair_solve_apply_u"):
             cur[0] += d
             cur[1] += 1
         if name == "rank_select":
