@@ -425,17 +425,18 @@ __device__ __attribute__((always_inline)) inline bool newton_pair(const double* 
   return true;
 }
 
-// LDS of a pair problem: the Jacobi sweeps', or Newton's.
+// LDS of a pair problem: the Jacobi sweeps', and in the same memory Newton's.
+// Waves drift apart between barriers, so each change of its use needs one after
+// the last access to the old contents and before the first to the new ones
+// (solve_pair: in hand_over, and where Newton's iteration has refused).
 template <bool NEWTON> struct PairLds {
   SolveLds jacobi;
-  __device__ NewtonLds& newton() { return *(NewtonLds*)nullptr; }
 };
 template <> struct PairLds<true> {
   union {
     SolveLds jacobi;
-    NewtonLds n;
+    NewtonLds newton;
   };
-  __device__ NewtonLds& newton() { return n; }
 };
 
 // Pair problem k of submatrix p in the given round (PS_NT threads); whether it
@@ -578,16 +579,21 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, bool qui
       *(double2*)&Rg[(row0 + m) * B2 + 62 - 2 * j] = make_double2(b1[m] * iB1, b0[m] * iB0);
     }
   };
+  // The columns t0 .. b1, scaled, become Newton's start X.
   auto hand_over = [&](const double (&t0)[PS_R], const double (&t1)[PS_R], const double (&b0)[PS_R],
                        const double (&b1)[PS_R], double iT0, double iT1, double iB0, double iB1) {
-    double (*X)[LS] = PL.newton().X;
+    __syncthreads();  // every wave has read its partial sums and norms, whose memory X takes
+    if constexpr (NEWTON) {
+      double (*X)[LS] = PL.newton.X;
 #pragma unroll
-    for (int m = 0; m < PS_R; ++m) {
-      X[row0 + m][2 * j] = t0[m] * iT0;
-      X[row0 + m][2 * j + 1] = t1[m] * iT1;
-      X[row0 + m][62 - 2 * j] = b1[m] * iB1;
-      X[row0 + m][63 - 2 * j] = b0[m] * iB0;
+      for (int m = 0; m < PS_R; ++m) {
+        X[row0 + m][2 * j] = t0[m] * iT0;
+        X[row0 + m][2 * j + 1] = t1[m] * iT1;
+        X[row0 + m][62 - 2 * j] = b1[m] * iB1;
+        X[row0 + m][63 - 2 * j] = b0[m] * iB0;
+      }
     }
+    __syncthreads();  // X is whole
   };
   bool converged = false;
   int par = 0;
@@ -595,7 +601,7 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, bool qui
   for (int sweep = 0; sweep < e.inner_max_sweeps; ++sweep) {
     if constexpr (NEWTON) {
       if (newton) {
-        if (newton_pair(B, Mp, I, J, fl, Rg, PL.newton(), start)) {
+        if (newton_pair(B, Mp, I, J, fl, Rg, PL.newton, start)) {
           if (threadIdx.x == 0) {
             *flagR = 1;
             atomicAdd(&e.stats[2 * p + 1], 1);
@@ -692,10 +698,8 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, bool qui
           hand_over(QT0, QT1, QB0, QB1, 1.0, 1.0, 1.0, 1.0);
         } else {
           exact_norms();
-          __syncthreads();  // the norms have been read; X takes their place
           hand_over(T0, T1, B0, B1, rsq_d(nT0), rsq_d(nT1), rsq_d(nB0), rsq_d(nB1));
         }
-        __syncthreads();
         newton = start = true;
       } else if (QUICK && quick) {
         converged = true;

@@ -111,6 +111,19 @@ def test_full_diag_sweep_limits(pf, n, max_sweeps):
     assert np.max(np.abs(A @ V - V * lam)) <= 1e-12
 
 
+@pytest.mark.parametrize("n", [200, 512])
+def test_full_diag_repeats_bitwise(pf, n):
+    """No wave's rotation depends on how far another has come: repeated full
+    diagonalisations, whose middle sweeps hand their columns over to Newton's
+    iteration, give the same bits every time."""
+    dev = torch.device("cuda:0")
+    A = torch.from_numpy(_random_symmetric(n, 3 * n) / np.sqrt(n)).to(dev)
+    full = pf.FullDiag(n)
+    runs = [[t.clone() for t in full.solve(A)] for _ in range(4)]
+    for lam, V in runs[1:]:
+        assert torch.equal(lam, runs[0][0]) and torch.equal(V, runs[0][1])
+
+
 @pytest.mark.parametrize("n,precision,tol", [(130, "fp64", 1e-12), (200, "fp64", 1e-12), (200, "mixed_bf16", 1e-8)])
 def test_late_sweeps(pf, n, precision, tol):
     """Submatrices that need more sweeps than are enqueued round by round (two

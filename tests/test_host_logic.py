@@ -29,3 +29,22 @@ def test_bench_flop_count_matches_the_step():
         assert abs(bench.algorithmic_flops(n, M, 2, 3) - (58.0 / 3.0 * n3 + 2.0 * n * n * M)) <= 1e-9 * n3
         assert abs(bench.algorithmic_flops(n, M, 1, 3) - (40.0 / 3.0 * n3 + 2.0 * n * n * M)) <= 1e-9 * n3
     assert abs(bench.algorithmic_flops(8192, 512, 2, 3) - 1.07e13) <= 0.01e13
+
+
+def test_pair_solver_lds_handover_has_barriers():
+    """The pair solver's Jacobi sweeps and Newton's iteration share their LDS.
+    Waves drift apart between barriers, so the hand-over must wait for every
+    wave's last reads of the old contents before it writes and for all writes
+    before anyone reads, Newton's LDS must be reached in no other way, and the
+    sweeps must wait again where Newton's iteration has refused."""
+    import re
+    src = open(os.path.join(ROOT, "paper_1502_07806_amd", "csrc", "eigh_jacobi.hip")).read()
+    src = re.sub(r"//[^\n]*", "", src)
+    body = src[src.index("__device__ bool solve_pair("):src.index("__device__ inline void solve_block(")]
+    m = re.search(r"auto hand_over = \[&\]\(.*?\) \{\n(.*?)\n  \};\n", body, re.S)
+    statements = [t.strip() for t in m.group(1).strip().split("\n") if t.strip()]
+    assert statements[0] == "__syncthreads();" and statements[-1] == "__syncthreads();"
+    rest = body.replace(m.group(0), "")
+    uses = re.findall(r"[^\n]*PL\.newton\b[^\n]*", rest)
+    assert len(uses) == 1 and "newton_pair(" in uses[0], uses
+    assert re.search(r"newton = false;\s*__syncthreads\(\);", rest)
