@@ -233,13 +233,16 @@ struct SolveLds {
 // iteration on the whole eigenvector matrix X of S (Ogita and Aishima's
 // refinement).  With R = I - X^T X and St = X^T S X,
 //   E_ij = R_ij / 2 + (St_ij + (l_i + l_j) R_ij / 2) / (l_j - l_i),
-//   E_ii = R_ii / 2,  X <- X + X E
+//   E_ii = R_ii / 2 + 3 R_ii^2 / 8,  X <- X + X E
 // squares the error of X.  The second term is formed from the same symmetric
 // St_ij for (i, j) and (j, i) and so is exactly antisymmetric: rounding
 // differences of St over a small gap would otherwise tilt the columns.  From
 // X = I the first step needs no product (E_ij = S_ij / (S_jj - S_ii)), each further one four 64 x 64 products on the
 // matrix cores.  It ends after a step with every |E_ij| <= 2^-30, whose square
-// is below the rounding.  A pair closer than its coupling allows (|E_ij| >
+// is below the rounding, and every |E_ii| <= 2^-19, whose cube is: where two
+// columns turn by t alone, their inner product is off by t^3 after the step, their
+// squared norms by t^2 (a column norm stayed off by 1e-13 with E_ii = R_ii / 2 and no
+// such test).  A pair closer than its coupling allows (|E_ij| >
 // 2^-8) is left unrotated when the coupling lies below the rotation floor, as
 // the sweeps' own test leaves it; otherwise, and when five steps do not do, the
 // result is false and the Jacobi sweeps take over.  About 12 us for one
@@ -250,6 +253,7 @@ struct SolveLds {
 // every sweep (eight levels at order 1024: 280 us a pair problem instead of 170).
 constexpr double NEWTON_MAX = 0.00390625;            // 2^-8
 constexpr double NEWTON_DONE = 9.313225746154785e-10;  // 2^-30
+constexpr double NEWTON_NORM = 1.9073486328125e-06;    // 2^-19
 constexpr double FINISH_ANGLE = 0.03125;             // 2^-5
 constexpr int NEWTON_STEPS = 5;
 struct NewtonLds {
@@ -369,7 +373,10 @@ __device__ __attribute__((always_inline)) inline bool newton_pair(const double* 
           const int i = row(ib), j = col(jb, r);
           const double rij = (i == j ? 1.0 : 0.0) - xx[ib][jb][r];
           double v = 0.5 * rij;
-          if (i != j) {
+          if (i == j) {  // 1 / sqrt(1 - R_ii) - 1 to second order
+            v = fma(0.75 * rij, v, v);
+            if (fabs(v) > NEWTON_NORM) flags |= 1;
+          } else {
             const double num = fma(0.5 * (L.lam[i] + L.lam[j]), rij, st[ib][jb][r]), gap = L.lam[j] - L.lam[i];
             if (fabs(num) <= NEWTON_MAX * fabs(gap)) v += num == 0.0 ? 0.0 : num / gap;
             else if (!(fabs(num) <= fl)) flags |= 2;

@@ -4,6 +4,7 @@
 #include "../common.h"
 #include "../gemm_x3.h"
 #include "../chol.h"
+#include "../eigh.h"
 #include "../gemm_oz.h"
 #include "../refine.h"
 
@@ -28,6 +29,35 @@ int pfsm_test_gemm_f64(int ta, int tb, int epi, int64_t M, int64_t N, int64_t K,
   g.M = M; g.N = N; g.K = K; g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc;
   g.alpha = alpha; g.beta = beta; g.eps = eps; g.D = D; g.ldd = ldd; g.part = part; g.lower_only = lower_only;
   return (int)gemm_f64(ta != 0, tb != 0, epi, g, (hipStream_t)stream);
+}
+
+// Submatrix eigensolver on one submatrix, the whole of At (n x n, column-major).
+// work: 256-byte aligned device memory of pfsm_test_eigh_bytes(n); it begins
+// with the diagonalised matrix and the accumulated eigenvectors (Mp x Mp each,
+// Mp = n rounded up to 64) and the two words of EighBatch::stats.  scal: the
+// Gershgorin scalars {step, low, high}; tab: zeros, with n as int32 at byte 8.
+static size_t eigh_work(EighBatch& e, int n, char* w) {
+  const int B2 = 2 * EIGH_B;
+  e.P = 1; e.Mp = (n + B2 - 1) / B2 * B2; e.nb = e.Mp / EIGH_B; e.inner_max_sweeps = EIGH_INNER_SWEEPS;
+  const size_t m2 = (size_t)e.Mp * e.Mp * sizeof(double), rw = (size_t)e.nb * B2 * B2 * sizeof(double);
+  e.Bw = (double*)w; e.Uw = (double*)(w + m2);
+  e.stats = (int*)(w + 2 * m2); e.state = e.stats + 64;
+  e.Rw = (double*)(w + 2 * m2 + 512); e.rflag = (int*)(w + 2 * m2 + 512 + rw); e.sel = e.rflag + e.nb;
+  return 2 * m2 + 512 + rw + (size_t)(e.nb + e.Mp) * sizeof(int);
+}
+int64_t pfsm_test_eigh_bytes(int n) {
+  EighBatch e = {};
+  return (int64_t)eigh_work(e, n, nullptr);
+}
+int pfsm_test_eigh(int n, const double* At, int max_sweeps, void* work, const double* scal, const void* tab, int* info,
+                   void* stream) {
+  EighBatch e = {};
+  eigh_work(e, n, (char*)work);
+  const char* t = (const char*)tab;
+  e.wstart = (const int64_t*)t; e.wsize = (const int32_t*)(t + 8); e.offset = (const int32_t*)(t + 16);
+  e.part_start = (const int64_t*)(t + 24);
+  e.scal = scal; e.info = info;
+  return (int)eigh_batched_run(e, At, n, max_sweeps, (hipStream_t)stream);
 }
 
 int pfsm_test_pack_x3(const void* X, int src_double, int64_t m, int64_t n, int64_t ldx, int flags, void* P,

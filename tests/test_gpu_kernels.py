@@ -151,6 +151,43 @@ def test_gemm_f64_epilogues(dev):
     assert np.max(np.abs(_np(C2)[low] - S[low])) <= tol
 
 
+@pytest.mark.parametrize("max_sweeps", [12])
+@pytest.mark.parametrize("n", [192, 512, 1000])
+def test_eigh_vectors_stay_orthonormal(dev, n, max_sweeps):
+    """The accumulated eigenvectors as the submatrix eigensolver leaves them,
+    before any orthonormalisation.  A round multiplies every column by a
+    rotation whose columns have norm 1 within the unit roundoff u, and its 64-term
+    products round once more, so after s sweeps of nb - 1 rounds V^T V is off
+    the identity by at most 2 u s (nb - 1), and the diagonal by as much times the
+    norm, at most 2, on top of the rotation floor (256 u norm)."""
+    L = lib()
+    g = np.random.default_rng(n)
+    A = g.standard_normal((n, n)) / np.sqrt(n)
+    A = 0.5 * (A + A.T)
+    r = np.sum(np.abs(A), 0) - np.abs(np.diag(A))
+    scal = torch.tensor([0.0, np.min(np.diag(A) - r), np.max(np.diag(A) + r)], dtype=torch.float64, device=dev)
+    tab = np.zeros(64, np.uint8)
+    tab[8:12] = np.frombuffer(np.int32(n).tobytes(), np.uint8)
+    tab = torch.from_numpy(tab).to(dev)
+    info = torch.zeros(1, dtype=torch.int32, device=dev)
+    work = torch.empty(L.pfsm_test_eigh_bytes(n), dtype=torch.uint8, device=dev)
+    dA = _cm(A, dev)
+    assert L.pfsm_test_eigh(n, _p(dA), max_sweeps, _p(work), _p(scal), _p(tab), _p(info), _stream()) == 0
+    assert int(info.item()) == 0
+    Mp = (n + 63) // 64 * 64
+    m2 = 8 * Mp * Mp
+    sweeps = int(work[2 * m2:2 * m2 + 4].view(torch.int32).item())
+    d = np.sort(_np(work[:m2].view(torch.float64).view(Mp, Mp).diagonal().contiguous())[:n])
+    U = _np(work[m2:2 * m2].view(torch.float64).view(Mp, Mp)[:n, :n])
+    bound = 2 * U64 * sweeps * (Mp // 32 - 1)
+    norm = np.max(np.abs(d))
+    lam = np.linalg.eigvalsh(A)
+    print("n %d limit %d: %d sweeps, V^T V - I %.2e, diagonal %.2e, bound %.2e" %
+          (n, max_sweeps, sweeps, np.max(np.abs(U @ U.T - np.eye(n))), np.max(np.abs(d - lam)), bound))
+    assert np.max(np.abs(U @ U.T - np.eye(n))) <= bound
+    assert np.max(np.abs(d - lam)) <= norm * bound + 256 * U64 * 2
+
+
 def _pack(x, by_rows, dev, flags_extra=0):
     L = lib()
     m, n = x.shape
