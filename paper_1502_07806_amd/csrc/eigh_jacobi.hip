@@ -454,7 +454,9 @@ template <> struct PairLds<true> {
 // past round 0, whose full tournament has rotated inside every block, only over
 // the 32 x 32 pairs with one column in each block: the top columns stay, the
 // bottom ones turn by one position a round, 32 rounds.  W's columns are not yet
-// orthogonal then, so R is the product of the rotations.  Far from convergence
+// orthogonal then, so R is the product of the rotations, its columns normalised
+// (up to 63 rotations leave a norm off by about 5 u, which added up over the
+// rounds: raw eigenvectors at order 1024 1.5e-13 from orthonormal).  Far from convergence
 // the outer sweeps reach no further with the pair problems solved to the end:
 // full diagonalisation at order 1024 takes 11 sweeps of 26 us a round instead of
 // 10 of 130 us (34.3 -> 17.6 ms), and 23 instead of 26 where eight levels
@@ -526,17 +528,18 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, bool qui
     B1[m] = shift(B1[m], row0 + m, 62 - 2 * j, cb);
     B0[m] = shift(B0[m], row0 + m, 63 - 2 * j, cb + 1);
   }
-  // exact squared norms of the lane's four columns (all start positions: the
-  // columns are back in place at the start of every sweep)
+  // exact squared norms of four columns held as the lane's (all start positions:
+  // the columns are back in place at the start of every sweep)
   double nT0, nT1, nB0, nB1;
-  auto exact_norms = [&]() {
+  auto exact_norms = [&](const double (&t0)[PS_R], const double (&t1)[PS_R], const double (&b0)[PS_R],
+                         const double (&b1)[PS_R]) {
     double a = 0.0, b = 0.0, c = 0.0, d = 0.0;
 #pragma unroll
     for (int m = 0; m < PS_R; ++m) {
-      a = fma(T0[m], T0[m], a);
-      b = fma(T1[m], T1[m], b);
-      c = fma(B1[m], B1[m], c);
-      d = fma(B0[m], B0[m], d);
+      a = fma(t0[m], t0[m], a);
+      b = fma(t1[m], t1[m], b);
+      c = fma(b1[m], b1[m], c);
+      d = fma(b0[m], b0[m], d);
     }
     *(double2*)&L.nrm[group][2 * j] = make_double2(a, b);
     *(double2*)&L.nrm[group][62 - 2 * j] = make_double2(c, d);
@@ -578,18 +581,21 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, bool qui
     b0 = b1;
     b1 = n1;
   };
+  // The columns t0 .. b1, normalised by the norms that exact_norms has just left,
+  // as the pair rotation, or as Newton's start X.
   auto store_rotation = [&](const double (&t0)[PS_R], const double (&t1)[PS_R], const double (&b0)[PS_R],
-                            const double (&b1)[PS_R], double iT0, double iT1, double iB0, double iB1) {
+                            const double (&b1)[PS_R]) {
+    const double iT0 = rsq_d(nT0), iT1 = rsq_d(nT1), iB0 = rsq_d(nB0), iB1 = rsq_d(nB1);
 #pragma unroll
     for (int m = 0; m < PS_R; ++m) {
       *(double2*)&Rg[(row0 + m) * B2 + 2 * j] = make_double2(t0[m] * iT0, t1[m] * iT1);
       *(double2*)&Rg[(row0 + m) * B2 + 62 - 2 * j] = make_double2(b1[m] * iB1, b0[m] * iB0);
     }
   };
-  // The columns t0 .. b1, scaled, become Newton's start X.
   auto hand_over = [&](const double (&t0)[PS_R], const double (&t1)[PS_R], const double (&b0)[PS_R],
-                       const double (&b1)[PS_R], double iT0, double iT1, double iB0, double iB1) {
+                       const double (&b1)[PS_R]) {
     __syncthreads();  // every wave has read its partial sums and norms, whose memory X takes
+    const double iT0 = rsq_d(nT0), iT1 = rsq_d(nT1), iB0 = rsq_d(nB0), iB1 = rsq_d(nB1);
     if constexpr (NEWTON) {
       double (*X)[LS] = PL.newton.X;
 #pragma unroll
@@ -624,7 +630,7 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, bool qui
       }
     }
     unsigned long long big = 0, wide = 0;  // lanes that rotated by more than the stopping / finishing angle
-    exact_norms();
+    exact_norms(T0, T1, B0, B1);
 #pragma unroll 1
     for (int r = 0; r < turns; ++r) {
       double p0 = 0.0, p1 = 0.0;
@@ -701,11 +707,12 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, bool qui
     if constexpr (NEWTON) {
       if (!wide && !start) {
         if (QUICK && quick) {
-          store_rotation(QT0, QT1, QB0, QB1, 1.0, 1.0, 1.0, 1.0);  // stands if Newton refuses
-          hand_over(QT0, QT1, QB0, QB1, 1.0, 1.0, 1.0, 1.0);
+          exact_norms(QT0, QT1, QB0, QB1);
+          store_rotation(QT0, QT1, QB0, QB1);  // stands if Newton refuses
+          hand_over(QT0, QT1, QB0, QB1);
         } else {
-          exact_norms();
-          hand_over(T0, T1, B0, B1, rsq_d(nT0), rsq_d(nT1), rsq_d(nB0), rsq_d(nB1));
+          exact_norms(T0, T1, B0, B1);
+          hand_over(T0, T1, B0, B1);
         }
         newton = start = true;
       } else if (QUICK && quick) {
@@ -721,10 +728,13 @@ __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, bool qui
   if (!converged && threadIdx.x == 0 && inf) atomicCAS(inf, 0, PFSM_INFO_EIGH_NOCONV);
   // eigenvectors: normalised columns of W, row-major: Rg[r * 2b + c] = R(r, c)
   if (QUICK && quick) {
-    if (!start) store_rotation(QT0, QT1, QB0, QB1, 1.0, 1.0, 1.0, 1.0);
+    if (!start) {
+      exact_norms(QT0, QT1, QB0, QB1);
+      store_rotation(QT0, QT1, QB0, QB1);
+    }
   } else {
-    exact_norms();
-    store_rotation(T0, T1, B0, B1, rsq_d(nT0), rsq_d(nT1), rsq_d(nB0), rsq_d(nB1));
+    exact_norms(T0, T1, B0, B1);
+    store_rotation(T0, T1, B0, B1);
   }
   if (threadIdx.x == 0) {
     *flagR = 1;

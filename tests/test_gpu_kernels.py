@@ -151,7 +151,7 @@ def test_gemm_f64_epilogues(dev):
     assert np.max(np.abs(_np(C2)[low] - S[low])) <= tol
 
 
-@pytest.mark.parametrize("max_sweeps", [12])
+@pytest.mark.parametrize("max_sweeps", [12, 40])  # every pair problem to the end; quick ones
 @pytest.mark.parametrize("n", [192, 512, 1000])
 def test_eigh_vectors_stay_orthonormal(dev, n, max_sweeps):
     """The accumulated eigenvectors as the submatrix eigensolver leaves them,
