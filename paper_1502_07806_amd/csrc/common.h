@@ -61,6 +61,7 @@ hipError_t gemm_f64(bool ta, bool tb, int epi, const GemmArgs& a, hipStream_t s)
 int gemm_f64_tile(int64_t M, int64_t N, bool lower);
 
 // ---------------------------------------------------------------- misc kernels
-hipError_t mirror_lower(double* C, int64_t n, int64_t ldc, hipStream_t s);
+// The upper triangle from the lower one; scale: both times *scale (device).
+hipError_t mirror_lower(double* C, int64_t n, int64_t ldc, hipStream_t s, const double* scale = nullptr);
 
 }  // namespace pfsm

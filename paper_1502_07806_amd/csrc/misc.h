@@ -18,12 +18,15 @@ hipError_t gershgorin_alpha(const double* At, int64_t n, int64_t ld, int q, doub
 hipError_t gershgorin_alpha(const float* At, int64_t n, int64_t ld, int q, double user_alpha,
                             double* part_lo, double* part_hi, double* scal, int* info, hipStream_t s);
 // Folded-spectrum polynomial of the iteration x <- x - alpha (A - eps)^q x taken
-// `iterations` times, about c = the middle of scal's Gershgorin interval:
-// coef[k n + j] = coefficient of (A - c)^k in (1 - alpha (A - eps_j)^q)^iterations,
-// k = 0 .. q iterations <= FS_POLY_MAX_DEGREE.
+// `iterations` times, in the operator B = (A - c) / h, c the middle and h the
+// power of two just below the width of scal's Gershgorin interval: with p_kj the
+// coefficient of B^k in (1 - alpha (A - eps_j)^q)^iterations, which is of order one
+// at any scale of A, and D = q iterations <= FS_POLY_MAX_DEGREE: coef[k n + j] =
+// p_kj where k is a multiple of block below D (it multiplies X0 itself), p_kj / h
+// elsewhere (it multiplies h B^r X0), and coef[(D + 1) n + j] = 1 / h.
 constexpr int FS_POLY_MAX_DEGREE = 8;
-hipError_t fs_poly_coefs(const double* eps, const double* scal, int64_t n, int q, int iterations, double* coef,
-                         hipStream_t s);
+hipError_t fs_poly_coefs(const double* eps, const double* scal, int64_t n, int q, int iterations, int block,
+                         double* coef, hipStream_t s);
 // Diagonal of A (ld = n): saved to keep and replaced by itself minus c (center
 // set), or put back from keep.
 hipError_t center_diag(double* A, int64_t n, double* keep, const double* scal, int center, hipStream_t s);

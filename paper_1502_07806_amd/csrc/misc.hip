@@ -91,11 +91,20 @@ __global__ __launch_bounds__(NT) void k_gersh_final(const double* lo, const doub
 
 __device__ inline double gersh_mid(const double* scal) { return 0.5 * (scal[1] + scal[2]); }
 
+// Exponent of the power of two h just below the Gershgorin interval's width
+// (0 for a width of zero or none).
+__device__ inline int gersh_exp(const double* scal) {
+  const double w = scal[2] - scal[1];
+  return w > 0.0 && isfinite(w) ? max(-1000, min(1000, ilogb(w))) : 0;
+}
+
 __global__ __launch_bounds__(NT) void k_fs_poly(const double* eps, const double* scal, int64_t n, int q,
-                                                int iterations, double* coef) {
+                                                int iterations, int block, double* coef) {
   const int64_t j = (int64_t)blockIdx.x * NT + threadIdx.x;
   if (j >= n) return;
-  const double a = scal[0], e = eps[j] - gersh_mid(scal);
+  const int x = gersh_exp(scal), D = q * iterations;
+  const double h = ldexp(1.0, x);
+  const double a = q == 2 ? scal[0] * h * h : scal[0] * h, e = ldexp(eps[j] - gersh_mid(scal), -x);
   const double b0 = q == 2 ? 1.0 - a * e * e : 1.0 + a * e, b1 = q == 2 ? 2.0 * a * e : -a, b2 = q == 2 ? -a : 0.0;
   double p[FS_POLY_MAX_DEGREE + 1];
 #pragma unroll
@@ -106,7 +115,8 @@ __global__ __launch_bounds__(NT) void k_fs_poly(const double* eps, const double*
       p[k] = b0 * p[k] + (k >= 1 ? b1 * p[k - 1] : 0.0) + (k >= 2 ? b2 * p[k - 2] : 0.0);
 #pragma unroll
   for (int k = 0; k <= FS_POLY_MAX_DEGREE; ++k)
-    if (k <= q * iterations) coef[(int64_t)k * n + j] = p[k];
+    if (k <= D) coef[(int64_t)k * n + j] = k % block == 0 && k < D ? p[k] : ldexp(p[k], -x);
+  coef[(int64_t)(D + 1) * n + j] = ldexp(1.0, -x);
 }
 
 __global__ __launch_bounds__(NT) void k_center_diag(double* A, int64_t n, double* keep, const double* scal,
@@ -275,7 +285,7 @@ __global__ void k_symmetrize(double* C, int64_t n, int64_t ldc) {
   }
 }
 
-__global__ void k_mirror_lower(double* C, int64_t n, int64_t ldc) {
+__global__ void k_mirror_lower(double* C, int64_t n, int64_t ldc, const double* scale) {
   __shared__ double a[32][33];
   const int64_t bi = blockIdx.x, bj = blockIdx.y;  // destination tile (bi < bj: strictly upper)
   if (bi > bj) return;
@@ -286,9 +296,15 @@ __global__ void k_mirror_lower(double* C, int64_t n, int64_t ldc) {
     a[r][tx] = (gi < n && gj < n) ? C[gi + gj * ldc] : 0.0;  // a[c][r] = C(bj*32 + r, bi*32 + c)
   }
   __syncthreads();
+  const double s = scale ? *scale : 1.0;
   for (int r = ty; r < 32; r += 8) {
     int64_t gi = bi * 32 + tx, gj = bj * 32 + r;  // destination (row gi, col gj) = C(gj, gi)
-    if (gi < n && gj < n && gi < gj) C[gi + gj * ldc] = a[tx][r];
+    if (gi < n && gj < n && gi < gj) C[gi + gj * ldc] = s * a[tx][r];
+  }
+  if (!scale) return;
+  for (int r = ty; r < 32; r += 8) {  // the source in place
+    int64_t gi = bj * 32 + tx, gj = bi * 32 + r;
+    if (gi < n && gj < n && gi >= gj) C[gi + gj * ldc] = s * a[r][tx];
   }
 }
 
@@ -398,9 +414,9 @@ hipError_t fill_i32(int* p, int64_t count, int value, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t mirror_lower(double* C, int64_t n, int64_t ldc, hipStream_t s) {
+hipError_t mirror_lower(double* C, int64_t n, int64_t ldc, hipStream_t s, const double* scale) {
   unsigned t = (unsigned)((n + 31) / 32);
-  hipLaunchKernelGGL(k_mirror_lower, dim3(t, t), dim3(256), 0, s, C, n, ldc);
+  hipLaunchKernelGGL(k_mirror_lower, dim3(t, t), dim3(256), 0, s, C, n, ldc, scale);
   return hipGetLastError();
 }
 
@@ -420,10 +436,11 @@ hipError_t gershgorin_alpha(const float* At, int64_t n, int64_t ld, int q, doubl
   return gershgorin_alpha_t(At, n, ld, q, user_alpha, part_lo, part_hi, scal, info, s);
 }
 
-hipError_t fs_poly_coefs(const double* eps, const double* scal, int64_t n, int q, int iterations, double* coef,
-                         hipStream_t s) {
+hipError_t fs_poly_coefs(const double* eps, const double* scal, int64_t n, int q, int iterations, int block,
+                         double* coef, hipStream_t s) {
   if (q * iterations > FS_POLY_MAX_DEGREE) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_fs_poly, dim3((unsigned)((n + NT - 1) / NT)), dim3(NT), 0, s, eps, scal, n, q, iterations, coef);
+  hipLaunchKernelGGL(k_fs_poly, dim3((unsigned)((n + NT - 1) / NT)), dim3(NT), 0, s, eps, scal, n, q, iterations, block,
+                     coef);
   return hipGetLastError();
 }
 

@@ -168,7 +168,9 @@ double eigh_angle(const pfsm_plan* pl) { return pl->precision == PFSM_PREC_MIXED
 // coefficients, every product with a power M_k, k >= 1, of the start vectors
 // runs over the submatrix rows only, the powers are symmetric (half a
 // product each), and ceil(D / s) - 1 whole products are left instead of
-// D - 1.  c is the middle of the Gershgorin interval, so that with the
+// D - 1.  The powers are kept over h^(k-1), h about the interval's width, so that
+// all have the size of At and no coefficient leaves the type's range
+// (fs_poly_coefs).  c is the middle of the Gershgorin interval, so that with the
 // automatic step length 1 / rho^q the terms' magnitudes sum to at most
 // 2^iterations (a caller's step length has no such bound, and more than four
 // iterations lose more than four bits: those go step by step).  At N = 8192,
@@ -433,7 +435,7 @@ pfsm_status pfsm_plan_create(pfsm_plan** out, const pfsm_desc* d) {
   if (pl->poly_block) {
     const size_t before = w;
     pl->p_mat = w; w = align256(w + fs_poly_matrices(pl) * N2);
-    pl->p_coef = w; w = align256(w + (size_t)(pl->q * pl->iterations + 1) * n * sizeof(double));
+    pl->p_coef = w; w = align256(w + (size_t)(pl->q * pl->iterations + 2) * n * sizeof(double));
     pl->p_diag = w; w = align256(w + n * sizeof(double));
     // a plan that fits the library's own workspace keeps fitting it
     if (before <= (size_t)PFSM_STATIC_SCRATCH_BYTES && w > (size_t)PFSM_STATIC_SCRATCH_BYTES) {
@@ -590,16 +592,17 @@ static pfsm_status solve_fp64(pfsm_plan* pl, const double* dA, int64_t lda, cons
     double* coef = (double*)(W + pl->p_coef);
     double* mat = (double*)(W + pl->p_mat);
     const size_t n2 = (size_t)n * n;
-    const double* M[4] = {nullptr, At, mat, mat + n2};  // powers 1 .. ps of At - c
+    const double* M[4] = {nullptr, At, mat, mat + n2};  // powers 1 .. ps of At - c, the k-th over h^(k-1)
+    const double* ih = coef + (int64_t)(D + 1) * n;     // 1 / h, n times
     double* blk[4] = {Wt, mat + (ps - 1) * n2, mat + ps * n2, mat + (ps + 1) * n2};
-    PFSM_TRY(fs_poly_coefs(eps, scal, n, pl->q, pl->iterations, coef, s));
+    PFSM_TRY(fs_poly_coefs(eps, scal, n, pl->q, pl->iterations, ps, coef, s));
     PFSM_TRY(center_diag(At, n, (double*)(W + pl->p_diag), scal, 1, s));
-    for (int k = 2; k <= ps; ++k) {  // M_k = M_1 M_(k-1), symmetric
+    for (int k = 2; k <= ps; ++k) {  // M_k = M_1 M_(k-1) / h, symmetric
       GemmArgs g = {};
       g.M = n; g.N = n; g.K = n; g.A = At; g.lda = n; g.B = M[k - 1]; g.ldb = n; g.C = (double*)M[k]; g.ldc = n;
       g.alpha = 1.0; g.lower_only = 1;
       PFSM_TRY(gemm_f64(true, false, EPI_STORE, g, s));
-      PFSM_TRY(mirror_lower((double*)M[k], n, n, s));
+      PFSM_TRY(mirror_lower((double*)M[k], n, n, s, ih));
     }
     // blk[b] = sum over its coefficients c_(ps b + k) M_k X0 (the last block's up to c_D)
     for (int k = 1; k <= ps; ++k) {
@@ -621,6 +624,7 @@ static pfsm_status solve_fp64(pfsm_plan* pl, const double* dA, int64_t lda, cons
       g.M = n; g.N = n; g.K = n; g.A = M[ps]; g.lda = n; g.B = blk[b + 1]; g.ldb = n; g.ldc = n;
       g.poly_count = 1;
       g.poly[0] = blk[b];
+      g.poly_coef[0] = ih;
       PFSM_TRY(gemm_f64(true, false, EPI_POLY, g, s));
     }
     if (pl->iterations <= 8) clk.mark(3 + 2 * pl->iterations);

@@ -103,6 +103,21 @@ def test_fs_polynomial(pf, q, iterations, shift):
     _compare(lam, Vo, lam_ref, V_ref, A)
 
 
+@pytest.mark.parametrize("scale", [1e60, 1e-60])
+@pytest.mark.parametrize("q,iterations", [(2, 3), (2, 4), (1, 4)])
+def test_fs_polynomial_scale(pf, q, iterations, scale):
+    """The polynomial form keeps the eigenvectors of a matrix of any scale at
+    which the folded-spectrum step itself stays in range (its powers and
+    coefficients would leave it unscaled: 1e60^8)."""
+    n, offs, halo = 601, uniform_layout(601, 90), 45
+    A, V, _, _ = prescribed_problem(n, n // 2, 1e-2, 6200 + 10 * q + iterations)
+    A, V = A.numpy(), V.numpy()
+    lam_ref, V_ref, info_ref = pfsm_ref(A, V, offs, halo, iterations, q)
+    _, info, lam, Vo = _run(pf, A * scale, V, offs, halo, iterations=iterations, fs_power=q)
+    assert info == info_ref == 0
+    _compare(lam / scale, Vo, lam_ref, V_ref, A)
+
+
 def test_single_full_window_matches_jacobi(pf):
     A, V, lam_ex, _ = prescribed_problem(192, 96, 1e-2, 55)
     A, V = A.numpy(), V.numpy()
