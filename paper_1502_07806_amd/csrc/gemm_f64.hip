@@ -654,10 +654,14 @@ hipError_t launch_tile(int epi, const GemmArgs& a, hipStream_t s) {
   // 16-byte loads need aligned columns and chunks that lie wholly inside or outside the matrix
   const bool wide = (((uintptr_t)a.A | (uintptr_t)a.B) & 15) == 0 && ((a.lda | a.ldb | a.M | a.N | a.K) & 1) == 0;
   if (a.lda >= (int64_t(1) << 21) || a.ldb >= (int64_t(1) << 21)) {
-    // offsets within a tile past 31 bits: the kernel with 64-bit ones
+    // offsets within a tile past 31 bits: the kernel with 64-bit ones, whose tile of
+    // 128 rows (which part_rows = 128 needs) has 32 columns.  A lower triangle
+    // needs square tiles and a product in place all columns in one: those take
+    // tiles of 64.
     if (tile == 32) return launch_epi<TA, TB, 1, 1, 32, int64_t>(epi, a, s);
-    return tile == 64 ? launch_epi<TA, TB, 2, 2, 16, int64_t>(epi, a, s)
-                      : launch_epi<TA, TB, 4, 1, 16, int64_t>(epi, a, s);
+    return tile == 64 || a.in_place || (a.lower_only && epi != EPI_RQ)
+               ? launch_epi<TA, TB, 2, 2, 16, int64_t>(epi, a, s)
+               : launch_epi<TA, TB, 4, 1, 16, int64_t>(epi, a, s);
   }
   if (tile == 32) return launch_epi<TA, TB, 1, 1, 32>(epi, a, s);
   if (tile == 64) return wide ? launch_dl<TA, TB, 2, 2, 16>(epi, a, s) : launch_dl<TA, TB, 2, 2, 4>(epi, a, s);

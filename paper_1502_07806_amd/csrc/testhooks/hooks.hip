@@ -28,6 +28,7 @@ int pfsm_test_gemm_f64(int ta, int tb, int epi, int64_t M, int64_t N, int64_t K,
   GemmArgs g = {};
   g.M = M; g.N = N; g.K = K; g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc;
   g.alpha = alpha; g.beta = beta; g.eps = eps; g.D = D; g.ldd = ldd; g.part = part; g.lower_only = lower_only;
+  g.in_place = C == A;
   return (int)gemm_f64(ta != 0, tb != 0, epi, g, (hipStream_t)stream);
 }
 

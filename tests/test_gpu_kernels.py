@@ -97,6 +97,43 @@ def test_gemm_f64_long_columns(dev):
     assert np.max(np.abs(dC.cpu().numpy().T - A @ B)) <= 18 * U64 * np.abs(A).max() * np.abs(B).max()
 
 
+@pytest.mark.parametrize("M,N,K,lower", [
+    (2433, 2433, 4, 1), (1300, 1300, 5, 1), (700, 700, 33, 1),  # lower triangles in tiles of 128, 64 and 32 elsewhere
+    (2433, 2433, 4, 0), (1300, 1282, 33, 0), (640, 33, 40, 0)])
+def test_gemm_f64_long_columns_tiles(dev, M, N, K, lower):
+    """Both operands with leading dimensions past the 31-bit tile offsets at the
+    orders of every tile size, whole and lower triangles.  Bound as above."""
+    ld = 1 << 21
+    g = torch.Generator(device=dev).manual_seed(M + N + K)
+    A, B = (torch.empty(K * ld, dtype=torch.float64, device=dev).view(K, ld) for _ in range(2))
+    A[:, :M] = torch.randn(K, M, generator=g, device=dev, dtype=torch.float64)
+    B[:, :N] = torch.randn(K, N, generator=g, device=dev, dtype=torch.float64)
+    C = torch.zeros((N, M), dtype=torch.float64, device=dev)
+    assert lib().pfsm_test_gemm_f64(0, 1, 0, M, N, K, _p(A), ld, _p(B), ld, _p(C), M, 1.0, 0.0, None, None, 0, None,
+                                    lower, _stream()) == 0
+    a, b = A[:, :M].cpu().numpy(), B[:, :N].cpu().numpy()
+    err = np.abs(C.cpu().numpy().T - a.T @ b)
+    if lower:
+        err = np.tril(err)
+    assert np.max(err) <= 2 * K * U64 * np.abs(a).max() * np.abs(b).max() * K
+
+
+def test_gemm_f64_long_columns_in_place(dev):
+    """The Cholesky panel's product over its own left operand (C = A, 64 columns)
+    at a number of rows whose tile is 128, with a leading dimension past the 31-bit
+    offsets: a row tile must stay with one workgroup.  Bound as above."""
+    M, N, ld = 32763, 64, 1 << 21
+    g = torch.Generator(device=dev).manual_seed(5)
+    A = torch.empty(N * ld, dtype=torch.float64, device=dev).view(N, ld)
+    A[:, :M] = torch.randn(N, M, generator=g, device=dev, dtype=torch.float64)
+    a = A[:, :M].cpu().numpy().T
+    T = torch.randn(N, N, generator=g, device=dev, dtype=torch.float64)
+    assert lib().pfsm_test_gemm_f64(0, 0, 0, M, N, N, _p(A), ld, _p(T), N, _p(A), ld, 1.0, 0.0, None, None, 0, None, 0,
+                                    _stream()) == 0
+    t = T.cpu().numpy().T
+    assert np.max(np.abs(A[:, :M].cpu().numpy().T - a @ t)) <= 2 * N * U64 * np.abs(a).max() * np.abs(t).max() * N
+
+
 @pytest.mark.parametrize("n", [127, 300, 515])
 def test_gemm_f64_rq_symmetric(dev, n):
     """Rayleigh quotients from the blocks of a symmetric matrix on and below

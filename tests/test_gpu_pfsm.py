@@ -118,6 +118,24 @@ def test_fs_polynomial_scale(pf, q, iterations, scale):
     _compare(lam / scale, Vo, lam_ref, V_ref, A)
 
 
+def test_basis_with_long_columns(pf):
+    """V_prev as columns of a far taller matrix (leading dimension 2^21) at an
+    order whose lower-triangle products run in tiles of 128: the eigenpairs of
+    the packed V_prev.  The sums may differ in order: n u times the norm of A
+    over the smallest gap (about 2e-4) for the vectors, n u for the values."""
+    n, ld = 2433, 1 << 21
+    dev = torch.device("cuda:0")
+    A, V, _, _ = prescribed_problem(n, n // 2, 1e-2, 6300)
+    A, V = A.to(dev), V.to(dev)
+    offs = uniform_layout(n, 256)
+    lam_ref, V_ref = (t.clone() for t in pf.Plan(n, offs, halo=128).solve(A, V))
+    tall = torch.empty(n * ld, dtype=torch.float64, device=dev).as_strided((n, n), (1, ld))
+    tall.copy_(V)
+    lam, Vo = pf.Plan(n, offs, halo=128).solve(A, tall)
+    assert torch.max(torch.abs(lam - lam_ref)).item() <= 2433 * 2.0 ** -53 * 4
+    assert torch.max(torch.abs(Vo - V_ref)).item() <= 1e-8
+
+
 def test_single_full_window_matches_jacobi(pf):
     A, V, lam_ex, _ = prescribed_problem(192, 96, 1e-2, 55)
     A, V = A.numpy(), V.numpy()
