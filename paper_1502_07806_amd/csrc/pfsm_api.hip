@@ -85,6 +85,7 @@ struct pfsm_plan {
   size_t m_Epk = 0, m_fm = 0;       // band form of the folded-spectrum products: off-diagonal At, far maxima
   // FP64 path: folded-spectrum iterations as one polynomial (0: step by step)
   int poly_block = 0;               // s: powers of At up to s, blocks of s coefficients
+  size_t step_total = 0;            // workspace without the polynomial's matrices
   size_t p_mat = 0, p_coef = 0, p_diag = 0;  // powers and blocks (n x n each), coefficients, diagonal of At
   size_t m_gcl = 0;                 // gate scalars of the orthonormalisation correction's band form
 };
@@ -194,6 +195,21 @@ int fs_poly_block(const pfsm_plan* pl) {
 size_t fs_poly_matrices(const pfsm_plan* pl) {
   const int D = pl->q * pl->iterations, s = pl->poly_block;
   return (size_t)(s - 1) + (size_t)((D + s - 1) / s - 1);
+}
+
+// The polynomial's matrices may fill a plan's workspace to at most half of the
+// device together with the solve's inputs and outputs (A, V_prev, V_out): an
+// order whose step by step form fits the card keeps fitting it, and leaves room
+// for other plans and the caller's data (one plan: n of about 46000).
+bool fs_poly_fits(double bytes, double n2_bytes) {
+  size_t mem = 0;
+  int dev = 0;
+  return hipGetDevice(&dev) == hipSuccess && hipDeviceTotalMem(&mem, dev) == hipSuccess &&
+         bytes + 3.0 * n2_bytes <= 0.5 * (double)mem;
+}
+void drop_fs_poly(pfsm_plan* pl) {
+  pl->poly_block = 0;
+  pl->total = pl->step_total;
 }
 
 // Submatrix eigensolver arguments: every pointer into the plan's workspace layout.
@@ -431,19 +447,18 @@ pfsm_status pfsm_plan_create(pfsm_plan** out, const pfsm_desc* d) {
     pl->m_fm = w; w = align256(w + (size_t)(2 * pl->iterations + 4) * sizeof(unsigned));
     pl->m_gcl = w; w = align256(w + 2 * sizeof(double));
   }
+  pl->step_total = w;
   pl->poly_block = fs_poly_block(pl);
   if (pl->poly_block) {
-    const size_t before = w;
     pl->p_mat = w; w = align256(w + fs_poly_matrices(pl) * N2);
     pl->p_coef = w; w = align256(w + (size_t)(pl->q * pl->iterations + 2) * n * sizeof(double));
     pl->p_diag = w; w = align256(w + n * sizeof(double));
-    // a plan that fits the library's own workspace keeps fitting it
-    if (before <= (size_t)PFSM_STATIC_SCRATCH_BYTES && w > (size_t)PFSM_STATIC_SCRATCH_BYTES) {
-      pl->poly_block = 0;
-      w = before;
-    }
   }
   pl->total = w;
+  // a plan that fits the library's own workspace keeps fitting it (callers of
+  // pfsm_solve_static go by pfsm_workspace_size)
+  const size_t own = (size_t)PFSM_STATIC_SCRATCH_BYTES;
+  if (pl->poly_block && ((pl->step_total <= own && w > own) || !fs_poly_fits((double)w, (double)N2))) drop_fs_poly(pl);
   *out = pl;
   return PFSM_OK;
 }
@@ -1083,6 +1098,15 @@ pfsm_status pfsm_plan_create_batched(pfsm_plan** out, const pfsm_desc* descs, in
       return st;
     }
     pl->sub.push_back(q);
+  }
+  double bytes = 0.0, n2_bytes = 0.0;
+  for (const pfsm_plan* q : pl->sub) {
+    bytes += (double)q->total;
+    n2_bytes += (double)q->n * q->n * sizeof(double);
+  }
+  const bool poly = fs_poly_fits(bytes, n2_bytes);
+  for (pfsm_plan* q : pl->sub) {
+    if (!poly && q->poly_block) drop_fs_poly(q);
     pl->sub_off.push_back(w);
     w = align256(w + q->total);
   }

@@ -136,6 +136,22 @@ def test_basis_with_long_columns(pf):
     assert torch.max(torch.abs(Vo - V_ref)).item() <= 1e-8
 
 
+def test_workspace_of_large_plans(pf):
+    """The polynomial's matrices (three of order n at three iterations) are part
+    of an FP64 plan's workspace only while they leave half of the card free: an
+    order that fits it step by step (a caller's step length always goes so) needs
+    no more, alone or in a batch."""
+    def bytes_of(n, alpha):
+        return pf.Plan(n, uniform_layout(n, 512), halo=256, alpha=alpha).workspace_bytes
+
+    assert bytes_of(8192, 0.0) - bytes_of(8192, 0.1) >= 3 * 8 * 8192 ** 2
+    assert bytes_of(60000, 0.0) == bytes_of(60000, 0.1)
+    n = 20000
+    batch = [pf.BatchedPlan([dict(n=n, part_offsets=uniform_layout(n, 512), halo=256, alpha=a)] * 8).workspace_bytes
+             for a in (0.0, 0.1)]
+    assert bytes_of(n, 0.0) > bytes_of(n, 0.1) and batch[0] == batch[1]
+
+
 def test_single_full_window_matches_jacobi(pf):
     A, V, lam_ex, _ = prescribed_problem(192, 96, 1e-2, 55)
     A, V = A.numpy(), V.numpy()
