@@ -32,6 +32,16 @@ int pfsm_test_gemm_f64(int ta, int tb, int epi, int64_t M, int64_t N, int64_t K,
   return (int)gemm_f64(ta != 0, tb != 0, epi, g, (hipStream_t)stream);
 }
 
+// Rayleigh quotient partials (and, with part2, the partial squared norms) of a
+// symmetric A in tiles of part_rows rows.
+int pfsm_test_gemm_f64_rq(int64_t n, const double* A, const double* X, double* part, double* part2, int part_rows,
+                          int lower_only, void* stream) {
+  GemmArgs g = {};
+  g.M = n; g.N = n; g.K = n; g.A = A; g.lda = n; g.B = X; g.ldb = n; g.D = X; g.ldd = n; g.alpha = 1.0;
+  g.part = part; g.part2 = part2; g.part_rows = part_rows; g.lower_only = lower_only;
+  return (int)gemm_f64(true, false, EPI_RQ, g, (hipStream_t)stream);
+}
+
 // Submatrix eigensolver on one submatrix, the whole of At (n x n, column-major).
 // work: 256-byte aligned device memory of pfsm_test_eigh_bytes(n); it begins
 // with the diagonalised matrix and the accumulated eigenvectors (Mp x Mp each,

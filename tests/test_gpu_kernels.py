@@ -155,6 +155,37 @@ def test_gemm_f64_rq_symmetric(dev, n):
     assert np.max(np.abs(rq - np.sum(X * (A @ X), 0))) <= tol
 
 
+@pytest.mark.parametrize("rows,n", [(32, 31), (32, 64), (32, 321), (64, 63), (64, 192), (64, 322), (64, 323),
+                                    (128, 127), (128, 256), (128, 386), (128, 387)])
+def test_gemm_f64_rq_part_rows(dev, rows, n):
+    """The Rayleigh quotients in every tile height, at orders below, at and above
+    multiples of it (even and odd: both load widths): from the blocks on and
+    below the diagonal, with NaN in all that lies past a tile's own diagonal
+    block, and whole with the squared norms of A X.  A quotient sums n^2 products
+    of three entries, a squared norm the n squares of sums of n products."""
+    g = np.random.default_rng(n + rows)
+    A = g.standard_normal((n, n))
+    A = 0.5 * (A + A.T)
+    X = g.standard_normal((n, n))
+    Al = A.copy()
+    for i in range(0, n, rows):
+        Al[i:i + rows, i + rows:] = np.nan
+    dA, dX = _cm(A, dev), _cm(X, dev)
+    dAl = _cm(Al.T.copy(), dev)  # op(A) = A^T
+    tiles = (n + rows - 1) // rows
+    part, part2 = (torch.full((tiles * n,), float("nan"), dtype=torch.float64, device=dev) for _ in range(2))
+    amax, xmax = np.abs(A).max(), np.abs(X).max()
+    tol = 2 * n * U64 * amax * xmax ** 2 * n ** 2
+    want = np.sum(X * (A @ X), 0)
+    assert lib().pfsm_test_gemm_f64_rq(n, _p(dAl), _p(dX), _p(part), None, rows, 1, _stream()) == 0
+    assert np.max(np.abs(_np(part).reshape(tiles, n).sum(0) - want)) <= tol
+    part.fill_(float("nan"))
+    assert lib().pfsm_test_gemm_f64_rq(n, _p(dA), _p(dX), _p(part), _p(part2), rows, 0, _stream()) == 0
+    assert np.max(np.abs(_np(part).reshape(tiles, n).sum(0) - want)) <= tol
+    tol2 = 4 * n * U64 * (amax * xmax * n) ** 2 * n
+    assert np.max(np.abs(_np(part2).reshape(tiles, n).sum(0) - np.sum((A @ X) ** 2, 0))) <= tol2
+
+
 def test_gemm_f64_epilogues(dev):
     n = 300
     g = np.random.default_rng(5)
