@@ -84,8 +84,10 @@ __device__ inline void pair_blocks(int k, int r, int nb, int& I, int& J) {
 // global index (within the padded submatrix) of local index t in [0, 2b) of pair (I, J)
 __device__ inline int pair_idx(int t, int I, int J) { return t < EIGH_B ? I * EIGH_B + t : J * EIGH_B + (t - EIGH_B); }
 
-// Counters of sweeps_left {tickets taken, tasks done}, in the ranking's memory,
-// which nothing uses before rank_select.
+// Counters of sweeps_left {tickets taken, tasks done}, LATE_DONE words apart (the
+// second is polled: a cache line of its own), in the ranking's memory of at least 64
+// ints, which nothing uses before rank_select.
+constexpr int LATE_DONE = 16;
 __device__ inline unsigned long long* late_counters(const EighBatch& e) { return (unsigned long long*)e.sel; }
 
 // ------------------------------------------------------------------ gather
@@ -110,7 +112,7 @@ __global__ void gather_windows(EighBatch e, const T* __restrict__ At, int64_t ld
     B[idx] = v;
     U[idx] = (r == c) ? 1.0 : 0.0;
   }
-  if (blockIdx.x == 0 && p == 0 && threadIdx.x < 2) late_counters(e)[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && p == 0 && threadIdx.x < 2) late_counters(e)[LATE_DONE * threadIdx.x] = 0;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     e.state[2 * p] = 0;      // last sweep that rotated (1-based)
     e.state[2 * p + 1] = 1;  // last sweep to run: the first one always does
@@ -977,15 +979,23 @@ __global__ __launch_bounds__(PS_NT, NEWTON ? 2 : 3) void pair_solve_apply_u(Eigh
 // whether the sweep runs before it waits for anything later.  A task's stores
 // are written back before it counts as done, and the caches invalidated after a
 // wait (the XCDs' L2s are not coherent), by one thread each: by all of them it
-// cost a third of the time.  One workgroup for a whole submatrix took eight times
-// as long (full diagonalisation at order 1024 of a matrix of eight levels, 26
-// sweeps: 1245 -> 180 ms); usual sweeps are faster in their own launches
-// (order 1024: 34 ms, all sweeps this way 58).
-constexpr int SL_NWG = 512;    // workgroups, and tasks of a round's tiles at most
+// cost a third of the time.
+//
+// What bounds it are those waits and fences; sweeps in their own launches are
+// faster, and with all sweeps in launches every solve would pay for the idle
+// ones.  From the identity basis, ten sweeps of which three (mixed) or four have
+// launches, against ten launched sweeps with their own tests of convergence:
+// order 4096 in eight submatrices of 1024 mixed 89 ms against 97, FP64 78 against
+// 100; order 2048 in eight of 512 mixed 33.0 against 35.5; two matrices of order
+// 1024 in a batch FP64 35 against 82 (all launched today: 24).  Of that, an acquire
+// or a release fence where a whole one stood, the polled counter in a line of its own
+// and polled less often gave 106 -> 100 ms at 4096 mixed, 384 workgroups for 512 (no
+// more than three tiles of a round each there) 89.
+constexpr int SL_NWG = 384;    // workgroups, and tasks of a round's tiles at most
 constexpr int SL_SCAN = 32;    // scan tasks per submatrix
 // Polls of a wait (some ten seconds) after which it reports non-convergence and
 // lets all waits through, so that even a broken order could not hang the queue.
-constexpr int SL_SPINS = 1 << 24;
+constexpr int SL_SPINS = 1 << 23;
 template <bool NEWTON, bool QUICK>
 __global__ __launch_bounds__(PS_NT, 2) void sweeps_left(EighBatch e, int first, int max_sweeps) {
   __shared__ union {
@@ -1007,15 +1017,15 @@ __global__ __launch_bounds__(PS_NT, 2) void sweeps_left(EighBatch e, int first, 
   auto wait = [&](u64 done) {
     if (threadIdx.x == 0) {
       int spins = 0;
-      while (__hip_atomic_load(&count[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < done) {
-        __builtin_amdgcn_s_sleep(2);
+      while (__hip_atomic_load(&count[LATE_DONE], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < done) {
+        __builtin_amdgcn_s_sleep(16);
         if (++spins == SL_SPINS) {
           for (int p = 0; p < e.P; ++p)
             if (int* inf = info_of(e, p)) atomicCAS(inf, 0, PFSM_INFO_EIGH_NOCONV);
-          atomicMax(&count[1], 1ull << 62);
+          atomicMax(&count[LATE_DONE], 1ull << 62);
         }
       }
-      __threadfence();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
   };
@@ -1069,8 +1079,8 @@ __global__ __launch_bounds__(PS_NT, 2) void sweeps_left(EighBatch e, int first, 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
-      __threadfence();
-      atomicAdd(&count[1], 1ull);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      atomicAdd(&count[LATE_DONE], 1ull);
     }
   }
 }
