@@ -245,8 +245,9 @@ struct SolveLds {
 // columns turn by t alone, their inner product is off by t^3 after the step, their
 // squared norms by t^2 (a column norm stayed off by 1e-13 with E_ii = R_ii / 2 and no
 // such test).  A pair closer than its coupling allows (|E_ij| >
-// 2^-8) is left unrotated when the coupling lies below the rotation floor, as
-// the sweeps' own test leaves it; otherwise, and when five steps do not do, the
+// 2^-8) is left unrotated when the coupling lies below a 32nd of the rotation floor,
+// 8 u of the norm, about where the sweeps' own test leaves it (at the floor itself the
+// pair stayed coupled where the sweeps resolve it); otherwise, and when five steps do not do, the
 // result is false and the Jacobi sweeps take over.  About 12 us for one
 // product step against 33 us for each Jacobi sweep of the 64 x 64 problem.
 // A Jacobi sweep whose rotations were all below FINISH_ANGLE also hands over:
@@ -256,6 +257,7 @@ struct SolveLds {
 constexpr double NEWTON_MAX = 0.00390625;            // 2^-8
 constexpr double NEWTON_DONE = 9.313225746154785e-10;  // 2^-30
 constexpr double NEWTON_NORM = 1.9073486328125e-06;    // 2^-19
+constexpr double NEWTON_LEFT = 0.03125;                // 2^-5
 constexpr double FINISH_ANGLE = 0.03125;             // 2^-5
 constexpr int NEWTON_STEPS = 5;
 struct NewtonLds {
@@ -381,7 +383,7 @@ __device__ __attribute__((always_inline)) inline bool newton_pair(const double* 
           } else {
             const double num = fma(0.5 * (L.lam[i] + L.lam[j]), rij, st[ib][jb][r]), gap = L.lam[j] - L.lam[i];
             if (fabs(num) <= NEWTON_MAX * fabs(gap)) v += num == 0.0 ? 0.0 : num / gap;
-            else if (!(fabs(num) <= fl)) flags |= 2;
+            else if (!(fabs(num) <= NEWTON_LEFT * fl)) flags |= 2;
             if (fabs(v) > NEWTON_DONE) flags |= 1;
           }
           st[ib][jb][r] = v;

@@ -219,19 +219,10 @@ def test_gemm_f64_epilogues(dev):
     assert np.max(np.abs(_np(C2)[low] - S[low])) <= tol
 
 
-@pytest.mark.parametrize("max_sweeps", [12, 40])  # every pair problem to the end; quick ones
-@pytest.mark.parametrize("n", [192, 512, 1000])
-def test_eigh_vectors_stay_orthonormal(dev, n, max_sweeps):
-    """The accumulated eigenvectors as the submatrix eigensolver leaves them,
-    before any orthonormalisation.  A round multiplies every column by a
-    rotation whose columns have norm 1 within the unit roundoff u, and its 64-term
-    products round once more, so after s sweeps of nb - 1 rounds V^T V is off
-    the identity by at most 2 u s (nb - 1), and the diagonal by as much times the
-    norm, at most 2, on top of the rotation floor (256 u norm)."""
+def _eigh(A, max_sweeps, dev):
+    """(diagonalised matrix, eigenvector rows, sweeps) of the submatrix eigensolver on all of A."""
     L = lib()
-    g = np.random.default_rng(n)
-    A = g.standard_normal((n, n)) / np.sqrt(n)
-    A = 0.5 * (A + A.T)
+    n = A.shape[0]
     r = np.sum(np.abs(A), 0) - np.abs(np.diag(A))
     scal = torch.tensor([0.0, np.min(np.diag(A) - r), np.max(np.diag(A) + r)], dtype=torch.float64, device=dev)
     tab = np.zeros(64, np.uint8)
@@ -244,9 +235,41 @@ def test_eigh_vectors_stay_orthonormal(dev, n, max_sweeps):
     assert int(info.item()) == 0
     Mp = (n + 63) // 64 * 64
     m2 = 8 * Mp * Mp
-    sweeps = int(work[2 * m2:2 * m2 + 4].view(torch.int32).item())
-    d = np.sort(_np(work[:m2].view(torch.float64).view(Mp, Mp).diagonal().contiguous())[:n])
-    U = _np(work[m2:2 * m2].view(torch.float64).view(Mp, Mp)[:n, :n])
+    B, U = (_np(work[o:o + m2].view(torch.float64).view(Mp, Mp)[:n, :n].contiguous()) for o in (0, m2))
+    return B, U, int(work[2 * m2:2 * m2 + 4].view(torch.int32).item())
+
+
+def test_eigh_close_pair_below_the_floor(dev):
+    """A pair problem that has to rotate also resolves a pair of equal diagonal
+    entries whose coupling lies below the rotation floor (256 u of the bound 2
+    on the norm).  The sweeps stop at inner products 8 u of the columns of S + sigma I,
+    sigma = 2 norm: |s| (2 + 2 + 2 sigma) <= 8 u (2 + sigma)^2, s = 24 u; two products of
+    64 terms of size 2 round by up to 8 u 2 each: 64 u covers both."""
+    n = 64
+    A = np.diag(np.linspace(1.0, 2.0, n))
+    A[11, 11] = A[10, 10]
+    A[10, 11] = A[11, 10] = 400 * U64
+    A[20, 40] = A[40, 20] = 3e-4  # a first-order rotation below 2^-8
+    B, U, _ = _eigh(A, 12, dev)
+    assert np.max(np.abs(B - np.diag(np.diag(B)))) <= 64 * U64
+    assert np.max(np.abs(U @ U.T - np.eye(n))) <= 64 * U64
+
+
+@pytest.mark.parametrize("max_sweeps", [12, 40])  # every pair problem to the end; quick ones
+@pytest.mark.parametrize("n", [192, 512, 1000])
+def test_eigh_vectors_stay_orthonormal(dev, n, max_sweeps):
+    """The accumulated eigenvectors as the submatrix eigensolver leaves them,
+    before any orthonormalisation.  A round multiplies every column by a
+    rotation whose columns have norm 1 within the unit roundoff u, and its 64-term
+    products round once more, so after s sweeps of nb - 1 rounds V^T V is off
+    the identity by at most 2 u s (nb - 1), and the diagonal by as much times the
+    norm, at most 2, on top of the rotation floor (256 u norm)."""
+    g = np.random.default_rng(n)
+    A = g.standard_normal((n, n)) / np.sqrt(n)
+    A = 0.5 * (A + A.T)
+    B, U, sweeps = _eigh(A, max_sweeps, dev)
+    d = np.sort(np.diag(B))
+    Mp = (n + 63) // 64 * 64
     bound = 2 * U64 * sweeps * (Mp // 32 - 1)
     norm = np.max(np.abs(d))
     lam = np.linalg.eigvalsh(A)
