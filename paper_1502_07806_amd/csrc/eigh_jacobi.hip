@@ -1153,11 +1153,14 @@ __global__ void embed_x0(EighBatch e, T* __restrict__ X, int64_t ldx, double* __
 
 }  // namespace
 
-// The last EXACT_SWEEPS sweeps of the limit solve their pair problems to the
-// end, as sweeps near convergence do anyway (Newton's iteration): below order
-// 256 clustered levels take up to twice the sweeps of quick ones, so a limit
-// near the usual count (the default, 10) is left as it was.
-constexpr int EXACT_SWEEPS = 12;
+// Quick pair problems only where the limit leaves room for sweeps that reach
+// less far: graded, cubic or clustered levels take one or two more of them than of
+// exact sweeps at order 200 to 400 (18 exact, 20 quick), up to twice as many
+// below, and as many or fewer from 512 on (29 at most, order 1024), so a limit
+// chosen near the count, and the default of 10, go exactly as far as it says.
+// The last EXACT_SWEEPS sweeps solve their pair problems to the end, as sweeps near
+// convergence do anyway (Newton's iteration).
+constexpr int QUICK_LIMIT = 40, EXACT_SWEEPS = 12;
 template <bool NEWTON, bool QUICK, typename T>
 static hipError_t eigh_run(const EighBatch& batch, const T* At, int64_t ldat, int max_sweeps, hipStream_t s) {
   EighBatch e = batch;
@@ -1198,7 +1201,7 @@ static hipError_t eigh_run(const EighBatch& batch, const T* At, int64_t ldat, in
 template <typename T>
 static hipError_t eigh_any(const EighBatch& e, const T* At, int64_t ldat, int max_sweeps, hipStream_t s) {
   if (e.floor_rel > 0.0) return eigh_run<false, false>(e, At, ldat, max_sweeps, s);
-  return max_sweeps > EXACT_SWEEPS ? eigh_run<true, true>(e, At, ldat, max_sweeps, s)
+  return max_sweeps >= QUICK_LIMIT ? eigh_run<true, true>(e, At, ldat, max_sweeps, s)
                                    : eigh_run<true, false>(e, At, ldat, max_sweeps, s);
 }
 

@@ -111,6 +111,22 @@ def test_full_diag_sweep_limits(pf, n, max_sweeps):
     assert np.max(np.abs(A @ V - V * lam)) <= 1e-12
 
 
+@pytest.mark.parametrize("n", [97, 300])
+def test_sweep_limit_is_only_a_limit(pf, n):
+    """Up to 39 the limit on the sweeps changes nothing but where they end: a
+    matrix that needs fewer than twelve has the same bits under every limit, so
+    that one whose count is close to its limit gets there too."""
+    dev = torch.device("cuda:0")
+    A = torch.from_numpy(_random_symmetric(n, 5 * n) / np.sqrt(n)).to(dev)
+    runs = []
+    for limit in (12, 13, 20, 39):
+        full = pf.FullDiag(n, limit)
+        runs.append([t.clone() for t in full.solve(A)])
+        assert full.plan.debug_stats()["converged_sweep"][0] < 12
+    for lam, V in runs[1:]:
+        assert torch.equal(lam, runs[0][0]) and torch.equal(V, runs[0][1])
+
+
 @pytest.mark.parametrize("n", [200, 512])
 def test_full_diag_repeats_bitwise(pf, n):
     """No wave's rotation depends on how far another has come: repeated full
