@@ -512,7 +512,7 @@ def main():
         upd_ms = st["fs_update_%d" % (n_it - 1)]  # one whole product
         dom_flops, peak, unit_dtype = 2.0 * n ** 3, PEAK_TFLOPS["fp64"], "f64"
         kname = "gemm_f64_dl<T,N,EPI_POLY> (folded-spectrum polynomial, %dx%dx%d, FP64 MFMA)" % (n, n, n)
-        kernel_key = "gemm_f64_fsupd_n%d" % n
+        kernel_key = "gemm_f64_poly_n%d" % n
     else:
         # the folded-spectrum update of the mixed path: one BF16 product from plain operands
         dom_flops, peak, unit_dtype = 2.0 * n ** 3, PEAK_TFLOPS["bf16"], "bf16"

@@ -463,8 +463,7 @@ template <> struct PairLds<true> {
 // rounds: raw eigenvectors at order 1024 1.5e-13 from orthonormal).  Far from convergence
 // the outer sweeps reach no further with the pair problems solved to the end:
 // full diagonalisation at order 1024 takes 11 sweeps of 26 us a round instead of
-// 10 of 130 us (34.3 -> 17.6 ms), and 23 instead of 26 where eight levels
-// cluster (171 -> 69 ms).
+// 10 of 130 us (34.3 -> 18.0 ms).
 template <bool NEWTON, bool QUICK>
 __device__ bool solve_pair(const EighBatch& e, int round, int p, int k, bool quick, PairLds<NEWTON>& PL) {
   SolveLds& L = PL.jacobi;

@@ -411,7 +411,8 @@ __global__ __launch_bounds__(NT, 3) void gemm_f64_kernel(GemmArgs g, int tiles_m
 // Bound by the FP64 matrix cores (64 cycles per MFMA): 75.0 TFLOP/s at N =
 // 8192 TN, 74 NN and NT (register-staged tiles with tested loads and both
 // halves' fragments read behind one barrier: 61, 50 and 57), tiles of 64 70
-// at 4096; 4-byte loads 71 and 65.  One workgroup of four 64 x 64 wave tiles
+// at 4096; 4-byte loads 71 and 65; with the polynomial's epilogue, whose loads
+// spill 108 registers a lane, 64.  One workgroup of four 64 x 64 wave tiles
 // per SIMD pair keeps two waves per SIMD, so that one's barrier skew hides
 // behind the other's MFMAs.  The compiler waits for every outstanding load
 // before an LDS read of a struct type (HIP's double2) but not of a vector

@@ -42,6 +42,14 @@ int pfsm_test_gemm_f64_rq(int64_t n, const double* A, const double* X, double* p
   return (int)gemm_f64(true, false, EPI_RQ, g, (hipStream_t)stream);
 }
 
+// P <- P + coef_j A B (n x n, A symmetric): a whole product of the folded-spectrum polynomial.
+int pfsm_test_gemm_f64_poly(int64_t n, const double* A, const double* B, double* P, const double* coef, void* stream) {
+  GemmArgs g = {};
+  g.M = n; g.N = n; g.K = n; g.A = A; g.lda = n; g.B = B; g.ldb = n; g.ldc = n;
+  g.poly_count = 1; g.poly[0] = P; g.poly_coef[0] = coef;
+  return (int)gemm_f64(true, false, EPI_POLY, g, (hipStream_t)stream);
+}
+
 // Submatrix eigensolver on one submatrix, the whole of At (n x n, column-major).
 // work: 256-byte aligned device memory of pfsm_test_eigh_bytes(n); it begins
 // with the diagonalised matrix and the accumulated eigenvectors (Mp x Mp each,

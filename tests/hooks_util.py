@@ -19,6 +19,8 @@ def lib():
         L.pfsm_test_gemm_f64.argtypes = [i32, i32, i32, i64, i64, i64, vp, i64, vp, i64, vp, i64, dbl, dbl, vp, vp,
                                          i64, vp, i32, vp]
         L.pfsm_test_gemm_f64.restype = i32
+        L.pfsm_test_gemm_f64_poly.argtypes = [i64, vp, vp, vp, vp, vp]
+        L.pfsm_test_gemm_f64_poly.restype = i32
         L.pfsm_test_gemm_f64_rq.argtypes = [i64, vp, vp, vp, vp, i32, i32, vp]
         L.pfsm_test_gemm_f64_rq.restype = i32
         L.pfsm_test_eigh_bytes.argtypes = [i32]

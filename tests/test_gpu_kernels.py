@@ -186,6 +186,20 @@ def test_gemm_f64_rq_part_rows(dev, rows, n):
     assert np.max(np.abs(_np(part2).reshape(tiles, n).sum(0) - np.sum((A @ X) ** 2, 0))) <= tol2
 
 
+@pytest.mark.parametrize("n", [100, 1301, 2046])  # tiles of 32, 64 and 128
+def test_gemm_f64_poly(dev, n):
+    """The polynomial epilogue's accumulating form.  Bound as above, coefficients of order one."""
+    g = np.random.default_rng(n)
+    A = g.standard_normal((n, n))
+    A = 0.5 * (A + A.T)
+    X, P = g.standard_normal((n, n)), g.standard_normal((n, n))
+    c = g.standard_normal(n)
+    dA, dX, dP, dc = _cm(A, dev), _cm(X, dev), _cm(P, dev), torch.from_numpy(c).to(dev)
+    assert lib().pfsm_test_gemm_f64_poly(n, _p(dA), _p(dX), _p(dP), _p(dc), _stream()) == 0
+    bound = 2 * n * U64 * (np.abs(A).max() * np.abs(X).max() * n * np.abs(c).max() + np.abs(P).max())
+    assert np.max(np.abs(_np(dP) - (P + (A @ X) * c))) <= bound
+
+
 def test_gemm_f64_epilogues(dev):
     n = 300
     g = np.random.default_rng(5)

@@ -48,3 +48,15 @@ def test_pair_solver_lds_handover_has_barriers():
     uses = re.findall(r"[^\n]*PL\.newton\b[^\n]*", rest)
     assert len(uses) == 1 and "newton_pair(" in uses[0], uses
     assert re.search(r"newton = false;\s*__syncthreads\(\);", rest)
+
+
+def test_bench_traffic_belongs_to_the_named_kernel():
+    """The FP64 roofline names the folded-spectrum polynomial's whole product and
+    takes its HBM bytes from that kernel's entry of the recorded traffic."""
+    import json
+    import re
+    bench = open(os.path.join(ROOT, "bench.py")).read()
+    key = re.search(r'EPI_POLY>[^\n]*\n\s*kernel_key = "(\w+)_n%d"', bench).group(1)
+    epi = re.search(r"EPI_POLY = (\d+)", open(os.path.join(ROOT, "paper_1502_07806_amd", "csrc", "common.h")).read()).group(1)
+    traffic = json.load(open(os.path.join(ROOT, "profiles", "traffic.json")))
+    assert traffic[key + "_n8192"]["kernel"].startswith("gemm_f64_dl<true, false, %s," % epi)

@@ -15,7 +15,7 @@ Dispatches, in order: a plain device copy of 1 GiB (calibration: 1 GiB read +
 1 GiB written), then at order n on synthetic operands: the split-BF16
 folded-spectrum update (FSUPD epilogue, default tile configuration), the same
 update from plain BF16 operands (one product, as the mixed path runs it), the
-FP64 folded-spectrum update, and the int8 digit product of the refinement
+whole product of the FP64 path's folded-spectrum polynomial, and the int8 digit product of the refinement
 (two digit splits with the refinement's digit count, then one launch).  Each counter value of a dispatch is
 scaled by the copy's bytes over the copy's counter value.  Needs
 libpfsm_testhooks.so (the internal kernels' test entry points).
@@ -68,7 +68,7 @@ def summarize(fetch_csv: str, write_csv: str, n: int, out: str):
                                     "by what the same counter reads for a 1 GiB device copy"}}
     for key, name in (("gemm_x3_fsupd_n%d" % n, "gemm_x3_dl<2, true, 3>"),
                       ("gemm_x3_fsupd_plain_n%d" % n, "gemm_x3_dl<2, true, 1>"),
-                      ("gemm_f64_fsupd_n%d" % n, "gemm_f64_dl"), ("gemm_oz_n%d" % n, OZ_PRODUCT)):
+                      ("gemm_f64_poly_n%d" % n, "gemm_f64_dl<true, false, 5, 4, 4, 16>"), ("gemm_oz_n%d" % n, OZ_PRODUCT)):
         f, w = pick(fe, name) * 1024 * sf, pick(wr, name) * 1024 * sw
         res[key] = {"kernel": name, "fetch_bytes": f, "write_bytes": w, "bytes_per_launch": f + w,
                     "source_hash": gemm_source_hash()}
@@ -140,8 +140,7 @@ def main():
     vp, i64, i32, dbl = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_double
     L.pfsm_test_gemm_x3.argtypes = [i32, i32, i32, i64, i64, i64, vp, i64, vp, i64, vp, i64, i32, dbl, dbl, vp, i64,
                                     vp, i64, i32, vp, vp, vp]
-    L.pfsm_test_gemm_f64.argtypes = [i32, i32, i32, i64, i64, i64, vp, i64, vp, i64, vp, i64, dbl, dbl, vp, vp, i64,
-                                     vp, i32, vp]
+    L.pfsm_test_gemm_f64_poly.argtypes = [i64, vp, vp, vp, vp, vp]
     L.pfsm_test_pack_x3.argtypes = [vp, i32, i64, i64, i64, i32, vp, i64, vp]
     L.pfsm_test_x3_row_stride.argtypes = [i64]
     L.pfsm_test_x3_row_stride.restype = i64
@@ -190,12 +189,11 @@ def main():
                                   0.1, s) == 0
     torch.cuda.synchronize()
     del Ap, Bp, Aq, Bq, Y32, X32
-    # FP64 folded-spectrum update, N x N x N
+    # a whole product of the FP64 folded-spectrum polynomial, N x N x N
     B = torch.randn(n, n, dtype=torch.float64, device=dev, generator=g)
     C = torch.randn(n, n, dtype=torch.float64, device=dev, generator=g)
     torch.cuda.synchronize()
-    assert L.pfsm_test_gemm_f64(0, 0, 2, n, n, n, P(M), n, P(B), n, P(C), n, 0.1, 0.0, P(eps), P(C), n, None, 0,
-                                s) == 0
+    assert L.pfsm_test_gemm_f64_poly(n, P(M), P(B), P(C), P(eps), s) == 0
     torch.cuda.synchronize()
     # int8 digit product with the refinement's digit count, C = M B
     s6 = L.pfsm_test_refine_slices()
